@@ -8,17 +8,26 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
   ProjPlan p{};
   if (rows_cap < 1) rows_cap = 1;
   if (dtype == 1) {   // fp32
+    // the tile height (32..128 rows) that pads the rows least, the tallest of
+    // equals (it reads W_U least); a launch that would leave most of the 256
+    // CUs idle takes 64 x 32 tiles instead
     p.variant = PROJ_F32;
-    p.rows_per_tile = 16;
-    p.vocab_cap = 64;
-    p.nvt = (V + 63) / 64;
-    p.nrt = (int)((rows_cap + 15) / 16);
-    p.split_rows = 0;
-    p.per_xcd = 0;
-    p.grid = p.nvt * p.nrt;
-    return p;
-  }
-  if (rows_cap <= kStreamMaxRows) {
+    p.vocab_cap = kF32TileVocab;
+    long long best = 0;
+    for (int tr = 128; tr >= 32; tr -= 32) {
+      const long long pad = (rows_cap + tr - 1) / tr * tr;
+      if (best == 0 || pad < best) {
+        best = pad;
+        p.rows_per_tile = tr;
+      }
+    }
+    p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
+    if ((long long)p.nvt * ((rows_cap + p.rows_per_tile - 1) / p.rows_per_tile) < 256) {
+      p.vocab_cap = kF32TileVocabSmall;
+      p.rows_per_tile = 32;
+      p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
+    }
+  } else if (rows_cap <= kStreamMaxRows) {
     // HBM-bound: one row tile holding every projected row, so W_U is read
     // once; a multiple of 256 equal vocabulary tiles, so every CU streams the
     // same share

@@ -61,6 +61,10 @@ size_t norm_bytes(const rpd_problem* p, long long cap) {
 // covered too.
 size_t workspace_bytes_for(const rpd_problem* p, long long cap) {
   const long long rows = (long long)p->K * cap;
+  if (p->dtype == RPD_DTYPE_F32)   // the smallest fp32 tile, which any row count may take
+    return kHeaderBytes + align256((size_t)((long long)p->B * p->L) * 4) +
+           align256((size_t)rows * ((p->V + rpd::kF32TileVocabSmall - 1) / rpd::kF32TileVocabSmall) * 16) +
+           lazy_bytes(cap) + norm_bytes(p, cap);
   size_t part = partial_bytes(rpd::plan_projection(p->dtype, rows, p->V), rows);
   for (long long r : {32LL, 33LL, 64LL, 65LL, 128LL, 129LL, 192LL, 193LL, 256LL, 257LL}) {
     const long long rr = r < rows ? r : rows;

@@ -10,7 +10,7 @@
 //                   softmax statistics folded in per vocabulary tile, so the
 //                   V-wide logits never reach memory (Section 2.2 readout;
 //                   Eq. 1 entropy); one variant per range of row counts
-//   k_proj_f32      the same on the vector ALU for fp32 inputs
+//   k_proj_f32      the same on the fp32 matrix cores for fp32 inputs
 //   k_reduce_score  merge of the per-tile statistics -> argmax, top
 //                   probability and entropy per layer; persistence (Eq. 2),
 //                   drop (Eq. 3), stability (Eq. 4) and candidacy (Eq. 5)

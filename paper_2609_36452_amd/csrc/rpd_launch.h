@@ -14,7 +14,7 @@ namespace rpd {
 enum ProjVariant {
   PROJ_BF16_S32 = 0,    // <= 32 rows: W_U streamed through wave-private LDS, hidden rows shared
   PROJ_BF16_S64 = 1,    // <= 64 rows, same kernel family
-  PROJ_F32 = 3,         // fp32 inputs: vector ALU, 16 rows x 64 vocab
+  PROJ_F32 = 3,         // fp32 inputs: fp32 MFMA tiles
   PROJ_BF16_BIG = 4,    // MFMA-bound: 256 x 256 tiles, both operands staged through LDS
   PROJ_BF16_BIG192 = 6, // the same kernel with 256 x 192 tiles (where they pad the rows less)
   PROJ_BF16_BIG128 = 7, // the same kernel with 256 x 128 tiles, for 65..128 rows
@@ -32,6 +32,9 @@ constexpr int kStreamTileVocab = 256;
 constexpr int kStreamMaxRows = 64;
 // rows of the smaller MFMA tiles
 constexpr int kBigTileRowsSmall = 192, kBigTileRowsMid = 128;
+// vocabulary rows of the fp32 tiles: the ordinary ones and, for launches too
+// small to fill the GPU, the small one
+constexpr int kF32TileVocab = 128, kF32TileVocabSmall = 64;
 // largest bound on a lazy pass's rows below which the host reads no count back
 constexpr int kLazyGateRows = 256;
 // largest canvas (B * L) whose compaction the streaming projection does itself

@@ -102,6 +102,38 @@ def test_bf16_variants(name, ov, seed, sharp):
         _check(w, P)
 
 
+# ------------------------------------------------------- fp32 MFMA tiles --
+
+F32_CASES = [
+    # projected rows 32, 64, 96 and 128 a tile, then the small tile (launches of under 256 tiles); hidden sizes of
+    # whole 32-wide chunks, with a tail, of one chunk, of none, and (d % 4 != 0) through 4-byte loads
+    ("tile32", dict(B=1, L=40, K=4, d=96, V=33001, n_masked=8), 61),
+    ("tile64_odd_d", dict(B=1, L=40, K=3, d=67, V=32900, n_masked=20), 62),
+    ("tile96_tail", dict(B=2, L=40, K=3, d=116, V=32769, n_masked=15), 63),
+    ("tile128_two_row_tiles", dict(B=1, L=64, K=4, d=32, V=16500, n_masked=60), 64),
+    ("tile128_odd_chunks", dict(B=1, L=64, K=3, d=161, V=32800, n_masked=42), 65),
+    ("tile64_row_split", dict(B=4, L=600, K=1, d=36, V=1500, n_masked=490), 66),
+    ("small_no_chunk", dict(B=1, L=40, K=4, d=20, V=700, n_masked=13), 67),
+    ("small_three_stages", dict(B=1, L=40, K=3, d=97, V=1025, n_masked=33), 68),
+]
+
+
+@pytest.mark.parametrize("name,ov,seed", F32_CASES, ids=[c[0] for c in F32_CASES])
+def test_f32_tiles(name, ov, seed):
+    base = CONFIGS["tiny"].with_(name="f32_" + name, sharp=("calibrated",), unstable_frac=0.3, **ov)
+    w = make_workload(base, seed)
+    _check(w, O.strict(base.K, 1.0))
+    hidden, w_u, mask = to_device(w)
+    # sources 4 bytes past a 16-byte boundary take the 4-byte loads: the sums keep their order, so the bits are equal
+    a = run_gpu(w, O.LLADA, tensors=(hidden, w_u, mask))
+    off = torch.empty(w_u.numel() + 1, dtype=w_u.dtype, device=w_u.device)[1:].view(w_u.shape)
+    off.copy_(w_u)
+    b = run_gpu(w, O.LLADA, tensors=(hidden, off, mask))
+    for k in a:
+        np.testing.assert_array_equal(a[k][..., w.mask != 0] if a[k].ndim >= 2 else a[k],
+                                      b[k][..., w.mask != 0] if b[k].ndim >= 2 else b[k], err_msg=k)
+
+
 # ------------------------------------------------------------ RPD-block --
 
 @pytest.mark.parametrize("block", [32, 1, 7, 48])
