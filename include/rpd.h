@@ -153,15 +153,19 @@ typedef struct rpd_problem {
  * persistence, drop and stability are then not evaluated (persistence -1,
  * drop and stability NaN). Either way tokens, candidacy and commitment are
  * those of the eager projection, and the per-layer outputs of layers never
- * projected hold -1 / NaN. One projection
- * pass per layer (each streams W_U again): it pays where the projection is
- * compute-bound (many masked positions), not where streaming W_U dominates.
- * While the bound on a pass's rows (max_masked, then the last count read
- * back) is at most 256, the pass reads its count on the device and is
- * launched once per size class the count may fall in (<= 64, <= 128, up to
- * the bound), all but one exiting at once; above, the previous pass's count
- * is read back (one stream synchronisation) and the pass planned for it. So
- * with max_masked <= 256 the call never synchronises.
+ * projected hold -1 / NaN. One projection pass takes as many of a position's
+ * next layers as cost no more than another pass would (each pass streams W_U
+ * again, and up to a few hundred rows that is what it costs), and a call so
+ * small that one pass over every layer costs no more than the final layer and
+ * the walk makes just that one; the layers below a position's first
+ * disagreement are then read and projected too, and reported as never
+ * projected. It pays where the projection is compute-bound (many masked
+ * positions). While max_masked is at most 256, every pass reads its count on
+ * the device and is launched once per size class the row count may fall in
+ * (<= 64, <= 128, <= 256, up to the bound; in fp32 32, 64, 128), all but one
+ * exiting at once; above, the previous pass's count is read back (one stream
+ * synchronisation) and the pass planned for it. So with max_masked <= 256 the
+ * call never synchronises.
  *
  * logit_scale multiplies every logit before the softmax statistics (an
  * inverse temperature). The paper reads probabilities before any

@@ -49,23 +49,26 @@ __device__ __forceinline__ void store_f64(float* p, long long k, double v) { p[k
 constexpr int kNormThreads = 256;
 
 // one workgroup per projected row r = p*K + l (r < n*K)
-// With an explicit row list (rowoff, a lazy pass over layer pass_layer),
-// row r < *n_ptr is hidden + rowoff[r]; otherwise rows are gathered for
-// r < *n_ptr * K.
+// With an explicit row list (rowoff, a lazy pass over *grp layers from *top
+// down), row r = j * *grp + g < *n_ptr is layer *top - g of listed position j;
+// otherwise rows are gathered for r < *n_ptr * K.
 template <typename T>
 __global__ __launch_bounds__(kNormThreads) void k_norm_rows(const T* __restrict__ hidden, const T* __restrict__ g,
                                                            const int32_t* __restrict__ rows,
                                                            const int32_t* __restrict__ n_ptr, T* __restrict__ xrows,
                                                            int K, int B, int L, int d, float eps, int norm_final,
-                                                           const long long* __restrict__ rowoff, int pass_layer) {
+                                                           const long long* __restrict__ rowoff,
+                                                           const int32_t* __restrict__ grp,
+                                                           const int32_t* __restrict__ top) {
   __shared__ double s_ss[kNormThreads / 64];
   const int r = blockIdx.x;
   int l;
   const T* src;
   if (rowoff) {
     if (r >= *n_ptr) return;
-    l = pass_layer;
-    src = hidden + rowoff[r];
+    const int G = *grp, j = r / G, g = r - j * G;
+    l = *top - g;
+    src = hidden + rowoff[j] - g * ((long long)B * L * d);
   } else {
     if (r >= *n_ptr * K) return;
     const int p = r / K;
@@ -106,12 +109,12 @@ hipError_t launch_norm_rows(const Launch& a, hipStream_t s) {
   if (a.plan.variant == PROJ_F32)
     hipLaunchKernelGGL(k_norm_rows<float>, grid, dim3(kNormThreads), 0, s, static_cast<const float*>(a.hidden),
                        static_cast<const float*>(a.norm_weight), a.rows, a.n_masked, static_cast<float*>(a.xrows),
-                       K, a.B, a.L, a.d, a.norm_eps, a.norm_final, a.rowoff, a.pass_layer);
+                       K, a.B, a.L, a.d, a.norm_eps, a.norm_final, a.rowoff, a.lazy.grp, a.lazy.top);
   else
     hipLaunchKernelGGL(k_norm_rows<uint16_t>, grid, dim3(kNormThreads), 0, s,
                        static_cast<const uint16_t*>(a.hidden), static_cast<const uint16_t*>(a.norm_weight), a.rows,
                        a.n_masked, static_cast<uint16_t*>(a.xrows), K, a.B, a.L, a.d, a.norm_eps, a.norm_final,
-                       a.rowoff, a.pass_layer);
+                       a.rowoff, a.lazy.grp, a.lazy.top);
   return hipGetLastError();
 }
 

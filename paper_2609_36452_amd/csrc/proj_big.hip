@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ w_u, const int32_t* __restrict__ rows,
     const int32_t* __restrict__ n_ptr, float4* __restrict__ partials, int K, int B, int L, int d, int V,
     int nvt, int nrt, int split_rows, const uint16_t* __restrict__ xrows, const long long* __restrict__ rowoff,
-    float scale) {
+    const int32_t* __restrict__ grp, float scale) {
   using namespace big;
   static_assert(TV == 256 && (TR == 256 || TR == 192 || TR == 128), "wave layout below assumes 256 x TR");
   constexpr int NB = TR / 64;   // 32-row fragment blocks of the hidden rows per wave
@@ -119,6 +119,7 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
   int pa[8];   // byte offsets of this lane's pieces from the tile's first W_U row (< 256 * d * 2)
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(w_u + (long long)vb * d), (short)0, (ve - vb) * d * 2, 0x00020000);
+  const int per = rowoff ? *grp : K;   // rows (layers) of a position
   // hidden-row sources: byte offsets from xsrc (HB) or addresses. Sized 8
   // (>= BL): an array sized by the template parameter, passed to the buffer
   // load builtin, made clang drop the kernel's host stub without a diagnostic.
@@ -141,13 +142,12 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
     long long ob;
     if (xrows) {   // normalized rows, already in projected-row order
       ob = (long long)r * d + piece * 8;
-    } else if (rowoff) {   // an explicit row list
-      ob = rowoff[r] + piece * 8;
     } else {
-      const int p = r / K, l = r - p * K;
-      const int pos = rows[p];
-      const int b = pos / L, i = pos - b * L;
-      ob = (((long long)l * B + b) * L + i) * (long long)d + piece * 8;
+      const int p = r / per, l = r - p * per;
+      if (rowoff)   // an explicit row list, its layers from the first one down
+        ob = rowoff[p] - l * ((long long)B * L * d) + piece * 8;
+      else
+        ob = ((long long)l * B * L + rows[p]) * (long long)d + piece * 8;
     }
     pb[u] = xsrc + ob;
     pbo[u] = (int)(ob * 2);
@@ -434,7 +434,7 @@ hipError_t launch_proj_big(const Launch& a, hipStream_t s) {
   hipLaunchKernelGGL(kernel, dim3(a.plan.grid), dim3(256), 0, s, static_cast<const uint16_t*>(a.hidden),
                      static_cast<const uint16_t*>(a.w_u), a.rows, a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V,
                      a.plan.nvt, a.plan.nrt, a.plan.split_rows, static_cast<const uint16_t*>(a.xrows), a.rowoff,
-                     a.logit_scale);
+                     a.lazy.grp, a.logit_scale);
   return hipGetLastError();
 }
 

@@ -53,7 +53,8 @@ template <int WV, int NB, int NS, bool V16>
 __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
     const float* __restrict__ hidden, const float* __restrict__ w_u, const int32_t* __restrict__ rows,
     const int32_t* __restrict__ n_ptr, float4* __restrict__ partials, int K, int B, int L, int d, int V, int nvt,
-    int nrt, int split_rows, const float* __restrict__ xrows, const long long* __restrict__ rowoff, float scale) {
+    int nrt, int split_rows, const float* __restrict__ xrows, const long long* __restrict__ rowoff,
+    const int32_t* __restrict__ grp, float scale) {
   constexpr int TV = 32 * WV, TR = 32 * NB, KC = 32;
   constexpr int RPI = V16 ? 8 : 2;             // rows per load instruction
   constexpr int AL = 32 / RPI;                 // W_U load instructions per wave per chunk
@@ -67,6 +68,7 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
   int rt, vt;
   if (!map_job(blockIdx.x, nvt, nrt, split_rows, rt, vt)) return;
   const int R = rowoff ? *n_ptr : *n_ptr * K;   // an explicit row list counts rows, not positions
+  const int G = rowoff ? *grp : 1;   // and this many layers of each listed position
   const int r0 = rt * TR;
   if (r0 >= R) return;
   const int vb = (int)((long long)vt * V / nvt);
@@ -96,7 +98,8 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
     if (xrows) {   // normalized rows, already in projected-row order
       pb[u] = xrows + (long long)r * d + kb[u];
     } else if (rowoff) {   // an explicit row list
-      pb[u] = hidden + rowoff[r] + kb[u];
+      const int j = r / G;
+      pb[u] = hidden + rowoff[j] - (r - j * G) * ((long long)B * L * d) + kb[u];
     } else {
       const int p = r / K, l = r - p * K;
       const int pos = rows[p];
@@ -249,7 +252,8 @@ void launch_f32(const Launch& a, hipStream_t s) {
   const auto kernel = v16 ? k_proj_f32<WV, NB, NS, true> : k_proj_f32<WV, NB, NS, false>;
   hipLaunchKernelGGL(kernel, dim3(p.grid), dim3(WV * 64), 0, s, static_cast<const float*>(a.hidden),
                      static_cast<const float*>(a.w_u), a.rows, a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V, p.nvt,
-                     p.nrt, p.split_rows, static_cast<const float*>(a.xrows), a.rowoff, a.logit_scale);
+                     p.nrt, p.split_rows, static_cast<const float*>(a.xrows), a.rowoff, a.lazy.grp,
+                     a.logit_scale);
 }
 
 }  // namespace

@@ -1,5 +1,7 @@
 // Host side of the projection: the tile plan for a row bound, and the
 // dispatch to the kernel variant it names.
+#include <algorithm>
+
 #include "rpd_launch.h"
 
 namespace rpd {
@@ -58,6 +60,34 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
   p.per_xcd = p.split_rows ? ((p.nrt + 7) / 8) * p.nvt : ((p.nvt + 7) / 8) * p.nrt;
   p.grid = 8 * p.per_xcd;
   return p;
+}
+
+// Time of one projection pass, for the lazy rules below: streaming W_U at the
+// rate the smallest row counts reach (6.7 TB/s in bf16, 5.6 in fp32), or the
+// rows' matrix time at the rate of 256 rows (1.05 PFLOP/s in bf16; 128 TFLOP/s
+// in fp32), whichever is more. kPassUs: what a pass costs besides, its
+// launches (up to four projections of which one runs, reduction, listing:
+// about 5 us each on the stream).
+static constexpr double kPassUs = 25.0;
+static double stream_us(int dtype, int d, int V) { return (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / 6.7e6); }
+static double row_us(int dtype, int d, int V) { return 2.0 * V * d / (dtype == 1 ? 128e6 : 1050e6); }
+
+int lazy_pass_rows(int dtype, int d, int V) {
+  const double r = (stream_us(dtype, d, V) + kPassUs) / row_us(dtype, d, V);
+  return r < 1.0 ? 1 : (r > 1e6 ? 1000000 : (int)r);
+}
+
+bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all) {
+  // One pass over everything against the least that walking can cost: the
+  // final layer of every position, and then empty passes (band), or one more
+  // layer of every position (walk_all, where every position walks).
+  const double st = stream_us(dtype, d, V), row = row_us(dtype, d, V);
+  const double one = std::max(st, row * (double)K * (double)cap);
+  const double first = std::max(st, row * (double)cap);
+  const int pr = lazy_pass_rows(dtype, d, V);
+  int passes = 0;
+  for (int rem = K - 1, g = 1; rem > 0; g *= 2, ++passes) rem -= lazy_group((int)std::max(cap, 1LL), rem, g, pr);
+  return one <= first + (walk_all && K > 1 ? first : 0.0) + kPassUs * passes;
 }
 
 hipError_t launch_projection(const Launch& a, hipStream_t s) {

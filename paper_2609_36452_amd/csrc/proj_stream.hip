@@ -105,7 +105,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ w_u, const int32_t* __restrict__ rows,
     const int32_t* __restrict__ n_ptr, float4* __restrict__ partials, int K, int B, int L, int d, int V,
     int nvt, int nrt, int split_rows, CompactArgs ca, const uint16_t* __restrict__ xrows,
-    const long long* __restrict__ rowoff, float scale) {
+    const long long* __restrict__ rowoff, const int32_t* __restrict__ grp, float scale) {
   constexpr int TR = 32 * NB, WR = 32 * MV, KC = 64, NT = NW * 64;
   constexpr int NLD = WR / 8;          // W_U load instructions per wave per chunk
   constexpr int XLD = TR * 8 / NT;     // hidden-row pieces per thread per chunk
@@ -147,9 +147,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
   // is read first (an empty launch then reads nothing: 1 us instead of 5).
   // Otherwise the W_U loads of the first two chunks go out before anything
   // waits.
-  int R = 0;
+  int R = 0, G = 1;   // G: layers taken of each listed position
   if (!FC && rowoff) {
     R = *n_ptr;
+    G = *grp;
     if (rt * TR >= R) return;
   }
   if (has_job && nchf > 0) {
@@ -183,7 +184,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
     if (xrows) {   // normalized rows, already in projected-row (or list) order
       xa[u] = (long long)r * d + xpiece[u] * 8;
     } else if (rowoff) {   // an explicit row list
-      xa[u] = rowoff[r] + xpiece[u] * 8;
+      const int j = r / G;
+      xa[u] = rowoff[j] - (r - j * G) * ((long long)B * L * d) + xpiece[u] * 8;
     } else {
       const int p = r / K, l = r - p * K;
       const int pos = FC ? s_pos[p] : rows[p];
@@ -323,12 +325,14 @@ void launch_stream(const Launch& a, hipStream_t s) {
     hipLaunchKernelGGL((k_proj_bf16_stream<NW, MV, NB, true>), dim3(p.grid), dim3(NW * 64), 0, s,
                        static_cast<const uint16_t*>(a.hidden), static_cast<const uint16_t*>(a.w_u), a.rows,
                        a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V, p.nvt, p.nrt, p.split_rows, ca,
-                       static_cast<const uint16_t*>(a.xrows), a.rowoff, a.logit_scale);
+                       static_cast<const uint16_t*>(a.xrows), a.rowoff, a.lazy.grp,
+                       a.logit_scale);
   else
     hipLaunchKernelGGL((k_proj_bf16_stream<NW, MV, NB, false>), dim3(p.grid), dim3(NW * 64), 0, s,
                        static_cast<const uint16_t*>(a.hidden), static_cast<const uint16_t*>(a.w_u), a.rows,
                        a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V, p.nvt, p.nrt, p.split_rows, ca,
-                       static_cast<const uint16_t*>(a.xrows), a.rowoff, a.logit_scale);
+                       static_cast<const uint16_t*>(a.xrows), a.rowoff, a.lazy.grp,
+                       a.logit_scale);
 }
 
 }  // namespace

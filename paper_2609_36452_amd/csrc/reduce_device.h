@@ -9,6 +9,24 @@
 namespace rpd {
 namespace {
 
+// The counts of a lazy pass over m positions and, from layer `top` down, g
+// layers of each (written by one thread): the row count also as the count of
+// the one size class it falls in, 0 in the other classes.
+__device__ __forceinline__ void list_pass(const LazyState& st, int m, int g, int top, const LazyClasses& c) {
+  const int n = m * g;
+  *st.m = m;
+  *st.grp = g;
+  *st.top = top;
+  *st.nrow = n;
+  int lo = 0;
+#pragma unroll
+  for (int k = 0; k < kLazyClasses; ++k) {
+    const int hi = k < kLazyClasses - 1 ? c.cap[k] : INT_MAX;
+    st.tier[k] = n > lo && n <= hi ? n : 0;
+    lo = hi;
+  }
+}
+
 // ------------------------------------------------------ exact argmax ties --
 //
 // The streaming projection takes each vocabulary tile's k-chunks in its own
@@ -160,6 +178,15 @@ __device__ __forceinline__ int resolve_tie(const Soft& s, const float4 (&keep)[8
   for (int u = 0; u < 8; ++u) batch(soft_unpack(keep[u]));
   for (int t0 = 512; t0 < nvt; t0 += 64) batch(t0 + lane < nvt ? soft_unpack(src[t0 + lane]) : soft_empty());
   return best;
+}
+
+// argmax (-1 if none), top probability 1/S and entropy ln S - T/S (Eq. 1) of
+// a merged state; NaN stays visible in the entropy
+__device__ __forceinline__ void state_stats(const Soft& s, int& y, float& c, float& h) {
+  const float e = fmaxf(logf(s.S) - s.T / s.S, 0.0f);
+  y = (s.idx == INT_MAX) ? -1 : s.idx;
+  c = 1.0f / s.S;
+  h = (s.S != s.S) ? s.S : e;
 }
 
 }  // namespace

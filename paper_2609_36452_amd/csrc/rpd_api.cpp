@@ -23,7 +23,7 @@ rpd_status fail(rpd_status s, const char* fmt, ...) {
   return s;
 }
 
-constexpr size_t kHeaderBytes = 256;   // n_masked (0), device status (4), lazy pass rows (12), by size class (16)
+constexpr size_t kHeaderBytes = 256;   // n_masked (0), device status (4), the lazy pass's counts (12..43)
 constexpr long long kMaxBL = 1LL << 24;
 constexpr int kMaxK = 64;
 // hidden sizes up to 2^20: the MFMA tile's 32-bit byte offsets within its
@@ -135,68 +135,81 @@ void fill_common(rpd::Launch& a, const rpd_params* q, const rpd_outputs* o) {
   a.user_status = o->status;
 }
 
-// Lazy layerwise projection: one projection pass per layer from the final
-// one down over the positions still walking their agreement suffix (rows
-// listed by k_lazy_next); how a pass is planned for a count that only the
-// device knows is described in the loop.
+// Lazy layerwise projection: projection passes from the final layer down over
+// the positions still walking their agreement suffix, each over as many
+// layers of them as lazy_group gives (rows listed by k_lazy_next); how a pass
+// is planned for a count that only the device knows is described in the loop.
 template <class Mark>
 hipError_t run_lazy(rpd::Launch& a, int dtype, hipStream_t s, Mark& mark) {
   hipError_t e = mark(1);
   if (e != hipSuccess) return e;
   if (a.max_masked > 0) {
-    int m_host = a.max_masked;   // pass 0, listed by the compaction: every masked position (<= max_masked)
+    int m_host = a.max_masked;   // bound on a pass's positions
+    const int pass_rows = rpd::lazy_pass_rows(dtype, a.d, a.V);
+    const rpd::LazyClasses cls = rpd::lazy_classes(dtype);
     // A pass runs the plan for its row count, which only the device knows.
-    // While the bound on it is at most kLazyGateRows the host reads nothing
-    // back: the pass is launched once per size class the count may fall in
-    // (<= 64 rows: streaming; <= 128; up to the bound), each taking its
-    // count from the device as that class's count, 0 unless it is the
-    // class, so all but one exit at once. Above the bound the count is read
-    // back (one stream synchronisation) and the pass planned for it. A
-    // single pass planned for the bound would run an MFMA tile whatever the
-    // count (lazy call at 256 positions: 838 -> 1010 us), and above 256 rows
-    // its few row tiles would land on a few XCDs.
-    // a pass over `cap` rows whose count is at `count`
-    auto pass_launch = [&](int l, int32_t* count, int cap) {
+    // While the bound on the positions is at most kLazyGateRows the host reads
+    // nothing back: the pass is launched once per size class the row count may
+    // fall in, each taking its count from the device as that class's count, 0
+    // unless it is the class, so all but one exit at once; and each pass takes
+    // at least twice the layers of the one before, so that few are enqueued.
+    // Above the bound the count is read back (one stream synchronisation) and
+    // the pass planned for it. A single pass planned for the bound would run
+    // an MFMA tile whatever the count (lazy call at 256 positions: 838 -> 1010
+    // us), and above 256 rows its few row tiles would land on a few XCDs.
+    // a pass of at most `cap` rows whose count is at `count`
+    auto pass_launch = [&](int32_t* count, long long cap) {
       rpd::Launch ap = a;
       ap.n_masked = count;
-      ap.max_masked = cap;
+      ap.max_masked = (int)cap;
       ap.rowoff = a.lazy.rowoff;
-      ap.pass_layer = l;
       ap.fused_compact = false;
       ap.plan = rpd::plan_projection(dtype, cap, a.V);
       return ap;
     };
-    for (int t = 0; t < a.K; ++t) {
-      const int l = a.K - 1 - t;
-      bool known = t == 0;
-      if (t > 0 && m_host > rpd::kLazyGateRows) {
-        int32_t m = 0;
-        if ((e = hipMemcpyAsync(&m, a.lazy.m, sizeof m, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (m <= 0) break;
-        m_host = m;
-        known = true;
+    // pass 0, listed by the compaction: the final layer of every masked position
+    int rem = a.K, group = 1, min_group = 1;
+    bool known = true;
+    for (int t = 0;; ++t) {
+      long long rows_cap = m_host;
+      if (t > 0) {
+        if ((e = rpd::launch_lazy_next(a, dtype, min_group, pass_rows, s)) != hipSuccess) return e;
+        known = m_host > rpd::kLazyGateRows;
+        if (known) {
+          int32_t m = 0;
+          if ((e = hipMemcpyAsync(&m, a.lazy.m, sizeof m, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+          if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+          if (m <= 0) break;
+          m_host = m;
+        }
+        // with the count known, the layers the device takes; else the fewest it may (it takes more of fewer positions)
+        group = rpd::lazy_group(m_host, rem, min_group, pass_rows);
+        rows_cap = known ? (long long)m_host * group
+                         : std::min((long long)m_host * rem,
+                                    std::max(2ll * pass_rows, (long long)m_host * min_group));
       }
       // the pass's rows are normalized once and reduced once; in between one
       // projection, or one per size class, of which only the count's class
       // writes the partials (the reduction takes that class's layout)
-      const rpd::Launch whole = pass_launch(l, a.lazy.m, m_host);
+      const rpd::Launch whole = pass_launch(a.lazy.nrow, rows_cap);
       if (whole.xrows && (e = rpd::launch_norm_rows(whole, s)) != hipSuccess) return e;
-      if (known || m_host <= rpd::kStreamMaxRows) {
+      if (known || rows_cap <= cls.cap[0]) {
         if ((e = rpd::launch_projection(whole, s)) != hipSuccess) return e;
-        if ((e = rpd::launch_lazy_reduce(whole, l, m_host, nullptr, s)) != hipSuccess) return e;
+        if ((e = rpd::launch_lazy_reduce(whole, dtype, m_host, nullptr, s)) != hipSuccess) return e;
       } else {
-        const int caps[3] = {rpd::kStreamMaxRows, std::min(m_host, rpd::kBigTileRowsMid), m_host};
-        const int ncls = m_host > rpd::kBigTileRowsMid ? 3 : 2;
-        rpd::ProjPlan plans[3];
-        for (int c = 0; c < 3; ++c) {
-          const rpd::Launch ap = pass_launch(l, a.lazy.tier + c, caps[c]);
+        rpd::ProjPlan plans[rpd::kLazyClasses];
+        for (int c = 0; c < rpd::kLazyClasses; ++c) {
+          const bool last = c == rpd::kLazyClasses - 1;
+          const rpd::Launch ap = pass_launch(a.lazy.tier + c, last ? rows_cap : std::min<long long>(rows_cap, cls.cap[c]));
           plans[c] = ap.plan;
-          if (c < ncls && (e = rpd::launch_projection(ap, s)) != hipSuccess) return e;
+          if (c > 0 && rows_cap <= cls.cap[c - 1]) continue;   // the count cannot be in this class
+          if ((e = rpd::launch_projection(ap, s)) != hipSuccess) return e;
         }
-        if ((e = rpd::launch_lazy_reduce(whole, l, m_host, plans, s)) != hipSuccess) return e;
+        if ((e = rpd::launch_lazy_reduce(whole, dtype, m_host, plans, s)) != hipSuccess) return e;
       }
-      if (l > 0 && (e = rpd::launch_lazy_next(a, l - 1, s)) != hipSuccess) return e;
+      rem -= group;
+      if (rem <= 0) break;
+      min_group = t == 0 || m_host > rpd::kLazyGateRows ? 1 : 2 * min_group;
     }
   }
   if ((e = mark(2)) != hipSuccess) return e;
@@ -330,11 +343,16 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
       lz += a4;
     }
     a.lazy.m = reinterpret_cast<int32_t*>(ws + 12);
-    a.lazy.tier = reinterpret_cast<int32_t*>(ws + 16);
+    a.lazy.grp = reinterpret_cast<int32_t*>(ws + 16);
+    a.lazy.top = reinterpret_cast<int32_t*>(ws + 20);
+    a.lazy.nrow = reinterpret_cast<int32_t*>(ws + 24);
+    a.lazy.tier = reinterpret_cast<int32_t*>(ws + 28);
   }
   a.rowoff = nullptr;
-  const bool lazy = (q->flags & RPD_PARAM_LAZY) != 0;
   fill_common(a, q, o);
+  // a lazy call is projected in passes, or all at once where that cannot cost more
+  const bool lazy_call = (q->flags & RPD_PARAM_LAZY) != 0;
+  bool lazy = lazy_call && !rpd::lazy_one_pass(p->dtype, a.K, a.max_masked, a.d, a.V, a.lazy_all);
 
   auto mark = [&](int k) -> hipError_t {
     if (k < n_events && events[k]) return hipEventRecord(static_cast<hipEvent_t>(events[k]), s);
@@ -348,7 +366,7 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
     a.fused_compact = !lazy && rpd::compact_fused(a);
   }
   hipError_t e = mark(0);
-  if (e == hipSuccess && !a.fused_compact) e = rpd::launch_compact(a, lazy, s);
+  if (e == hipSuccess && !a.fused_compact) e = rpd::launch_compact(a, lazy, p->dtype, s);
   if (e != hipSuccess) return fail(RPD_ERR_HIP, "compaction: %s", hipGetErrorString(e));
   if (p->max_masked < 0) {
     int32_t n = 0;
@@ -357,7 +375,9 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
     if (e != hipSuccess) return fail(RPD_ERR_HIP, "reading the masked count: %s", hipGetErrorString(e));
     a.max_masked = n;
     a.plan = rpd::plan_projection(p->dtype, (long long)p->K * a.max_masked, p->V);
+    lazy = lazy && !rpd::lazy_one_pass(p->dtype, a.K, n, a.d, a.V, a.lazy_all);
   }
+  a.lazy_score = lazy_call && !lazy;
   if (lazy) {
     e = run_lazy(a, p->dtype, s, mark);
   } else if ((e = mark(1)) == hipSuccess && (!a.xrows || (e = rpd::launch_norm_rows(a, s)) == hipSuccess) &&

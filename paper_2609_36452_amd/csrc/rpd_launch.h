@@ -35,8 +35,18 @@ constexpr int kBigTileRowsSmall = 192, kBigTileRowsMid = 128;
 // vocabulary rows of the fp32 tiles: the ordinary ones and, for launches too
 // small to fill the GPU, the small one
 constexpr int kF32TileVocab = 128, kF32TileVocabSmall = 64;
-// largest bound on a lazy pass's rows below which the host reads no count back
+// largest bound on a lazy call's positions below which the host reads no count back
 constexpr int kLazyGateRows = 256;
+// size classes of a lazy pass whose row count only the device knows: the
+// largest count of each class but the last (which holds the rest), by type;
+// each is the largest count of a projection variant
+constexpr int kLazyClasses = 4;
+struct LazyClasses {
+  int cap[kLazyClasses - 1];
+};
+inline LazyClasses lazy_classes(int dtype) {
+  return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 256}};
+}
 // largest canvas (B * L) whose compaction the streaming projection does itself
 constexpr int kFusedCompactMax = 2048;
 
@@ -54,10 +64,28 @@ struct ProjPlan {
 // the shape plan for `rows_cap` rows (K * max masked positions)
 ProjPlan plan_projection(int dtype, long long rows_cap, int V);
 
+// Lazy projection (proj_plan.cpp): the rows whose matrix time is that of one
+// more pass (at least 1)
+int lazy_pass_rows(int dtype, int d, int V);
+// whether a lazy call over at most `cap` positions projects all K layers of
+// every position in one pass
+bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all);
+// Layers that the next lazy pass takes of each of its m positions, `rem`
+// layers being left: all of them while that is no more than twice the rows a
+// pass is worth, else as many as a pass is worth, at least min_group. Never
+// fewer for fewer positions.
+__host__ __device__ inline int lazy_group(int m, int rem, int min_group, int pass_rows) {
+  if (m <= 0 || rem <= 0) return 0;
+  if ((long long)m * rem <= 2ll * pass_rows) return rem;
+  int g = pass_rows / m;
+  g = g < min_group ? min_group : g;
+  return g < rem ? g : rem;
+}
+
 // per-position state of the lazy layerwise projection (lazy.hip)
 struct LazyState {
   int32_t* act;        // [cap] compacted positions listed for the current pass
-  long long* rowoff;   // [cap] element offsets into hidden of their rows
+  long long* rowoff;   // [cap] element offsets into hidden of their rows at the pass's first layer
   int32_t* y;          // [cap] final-layer token
   float* c;            // [cap] final-layer top probability
   float* h;            // [cap] final-layer entropy
@@ -65,8 +93,11 @@ struct LazyState {
   float* pmax;         // [cap] peak top probability over the suffix
   int32_t* alive;      // [cap] 1 while the walk continues
   int32_t* depth;      // [cap] layers projected
-  int32_t* m;          // [1] rows in the current pass
-  int32_t* tier;       // [3] the same count in its size class (<= 64, <= 128, above), 0 in the others
+  int32_t* m;          // [1] positions in the current pass
+  int32_t* grp;        // [1] layers it takes of each
+  int32_t* top;        // [1] the first (highest) of these layers
+  int32_t* nrow;       // [1] rows in the current pass (m * grp)
+  int32_t* tier;       // [kLazyClasses] the row count in its size class, 0 in the others
 };
 
 struct LazyScoreArgs {
@@ -105,10 +136,11 @@ struct Launch {
   float norm_eps;
   int norm_final;
   void* xrows;
-  // explicit row list (lazy passes): projected row r is hidden + rowoff[r]
-  // (with K == 1 and n_masked pointing at the row count); NULL: gathered
+  // explicit row list (lazy passes): projected row r = j * G + g, with G at
+  // lazy.grp, is layer g below the pass's first one of listed position j, at
+  // hidden + rowoff[j] - g * B * L * d (n_masked points at the row count);
+  // NULL: gathered
   const long long* rowoff;
-  int pass_layer;        // the layer of an explicit row list (normalization)
   LazyState lazy;
   ProjPlan plan;
   // params
@@ -117,6 +149,7 @@ struct Launch {
   int block;             // 0: full RPD; > 0: RPD-block
   float logit_scale;     // multiplies every logit before the softmax statistics
   bool lazy_all;         // lazy projection: every masked position walks its layers (RPD_PARAM_LAZY_ALL)
+  bool lazy_score;       // a lazy call projected in one pass: the scoring reports what the walk would have
   // outputs
   uint8_t* commit; int32_t* token; float* entropy; float* confidence;
   int32_t* persistence; float* drop; float* stability; uint8_t* flags;
@@ -127,18 +160,19 @@ struct Launch {
 
 // enqueue, in this order: compaction, projection, reduction + scoring,
 // commitment (the last three use a.plan and a.max_masked)
-// lazy_list: also list the first lazy pass (a.lazy: act, rowoff, m, tier)
-hipError_t launch_compact(const Launch& a, bool lazy_list, hipStream_t s);
+// lazy_list: also list the first lazy pass (a.lazy), of type dtype
+hipError_t launch_compact(const Launch& a, bool lazy_list, int dtype, hipStream_t s);
 hipError_t launch_projection(const Launch& a, hipStream_t s);
 hipError_t launch_reduce_score(const Launch& a, hipStream_t s);
 hipError_t launch_commit(const Launch& a, hipStream_t s);
 
-// lazy layerwise projection: list the rows of layer l still walking,
-// reduce a pass over layer l, score from the per-position state
-hipError_t launch_lazy_next(const Launch& a, int l, hipStream_t s);
-// class_plans: the plans for rows <= 64, <= 128 and above, when the pass
-// ran once per size class (NULL: a.plan)
-hipError_t launch_lazy_reduce(const Launch& a, int l, int m_cap, const ProjPlan* class_plans, hipStream_t s);
+// lazy layerwise projection: list the next pass (the positions still walking
+// and the layers it takes of each, lazy_group), reduce a pass, score from the
+// per-position state
+hipError_t launch_lazy_next(const Launch& a, int dtype, int min_group, int pass_rows, hipStream_t s);
+// m_cap: bound on the pass's positions; class_plans: the plans of the size
+// classes, when the pass ran once per class (NULL: a.plan)
+hipError_t launch_lazy_reduce(const Launch& a, int dtype, int m_cap, const ProjPlan* class_plans, hipStream_t s);
 hipError_t launch_lazy_score(const Launch& a, hipStream_t s);
 // the projection does the compaction itself (needs a.plan and a.max_masked
 // >= 0): the call then launches no compaction kernel

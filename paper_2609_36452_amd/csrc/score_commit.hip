@@ -11,16 +11,13 @@ namespace {
 // ------------------------------------------------------------ K0 compact --
 
 // With lazy projection the compaction also lists the first pass (the final
-// layer of every masked position, in order): act, the rows' element offsets,
-// the count and its size class (<= t0, <= t1, above) as k_lazy_next writes
-// them for the later passes.
+// layer of every masked position, in order) as k_lazy_next lists the later
+// ones.
 struct FirstPassList {
-  int32_t* act;          // NULL: no listing
-  long long* rowoff;
-  int32_t* m;
-  int32_t* tier;
+  LazyState st;          // act NULL: no listing
   long long layer_off;   // (K-1) * B * L: the final layer's first row
-  int d, t0, t1;
+  int K, d;
+  LazyClasses cls;
 };
 
 __global__ __launch_bounds__(1024) void k_compact(const uint8_t* __restrict__ mask, int BL, int cap,
@@ -46,9 +43,9 @@ __global__ __launch_bounds__(1024) void k_compact(const uint8_t* __restrict__ ma
     const int pos = carry + off + before;
     if (f && pos < cap) {
       rows[pos] = i;
-      if (fp.act) {
-        fp.act[pos] = pos;
-        fp.rowoff[pos] = (fp.layer_off + i) * fp.d;
+      if (fp.st.act) {
+        fp.st.act[pos] = pos;
+        fp.st.rowoff[pos] = (fp.layer_off + i) * fp.d;
       }
     }
     carry += tot;
@@ -63,12 +60,7 @@ __global__ __launch_bounds__(1024) void k_compact(const uint8_t* __restrict__ ma
     *n_out = n;
     *dev_status = st;
     if (user_status) *user_status = st;
-    if (fp.act) {
-      *fp.m = n;
-      fp.tier[0] = n <= fp.t0 ? n : 0;
-      fp.tier[1] = n > fp.t0 && n <= fp.t1 ? n : 0;
-      fp.tier[2] = n > fp.t1 ? n : 0;
-    }
+    if (fp.st.act) list_pass(fp.st, n, 1, fp.K - 1, fp.cls);
   }
 }
 
@@ -98,6 +90,7 @@ struct ScoreArgs {
   int32_t* layer_argmax;
   float* layer_conf;
   float* layer_entropy;
+  int lazy;   // 0: eager; 1, 2: report what a lazy walk of the band / of every position would have projected
 };
 
 // One workgroup of four waves per masked position. Wave w merges the
@@ -106,16 +99,6 @@ struct ScoreArgs {
 // xor butterfly combines the lanes. Wave 0 then evaluates persistence, drop
 // and stability with one lane per layer.
 constexpr int kReduceWaves = 4;
-
-// argmax (-1 if none), top probability 1/S and entropy ln S - T/S (Eq. 1) of
-// a merged state; NaN stays visible in the entropy
-__device__ __forceinline__ void state_stats(const Soft& s, int& y, float& c, float& h) {
-  const float e = fmaxf(logf(s.S) - s.T / s.S, 0.0f);
-  y = (s.idx == INT_MAX) ? -1 : s.idx;
-  c = 1.0f / s.S;
-  h = (s.S != s.S) ? s.S : e;
-}
-
 
 // Eq. 2-5 for one position from its per-layer argmax / top probability /
 // entropy (layer l at offset l * stride), evaluated sequentially from the
@@ -444,24 +427,29 @@ __global__ __launch_bounds__(64 * kReduceWaves) void k_reduce_score(const float4
       float pk = (lane >= a.K - k_i && lane < a.K) ? my_c : -INFINITY;
 #pragma unroll
       for (int m = 32; m >= 1; m >>= 1) pk = fmaxf(pk, __shfl_xor(pk, m));
-      const float r_i = pk - cK;
-      const float s_i = stability_score(k_i, r_i, a.k_max, a.w);
+      // a lazy call evaluates stability where the position walks, and
+      // projects the layers down to the first disagreeing one there
+      const bool walks = a.lazy == 0 || (a.lazy == 2 ? cK == cK : (cK >= a.theta_c && cK < a.theta_h));
+      const int seen = a.lazy == 0 ? a.K : (walks ? min(a.K, k_i + 1) : 1);
+      const float r_i = walks ? pk - cK : NAN;
+      const float s_i = walks ? stability_score(k_i, r_i, a.k_max, a.w) : NAN;
       const unsigned fl = route_flags(cK, s_i, a.theta_h, a.theta_c, a.theta_s);
       const long long o = (long long)b * a.L + i;
       if (lane == 0) {
         a.token[o] = yK;
         a.entropy[o] = hK;
         a.confidence[o] = cK;
-        a.persistence[o] = k_i;
+        a.persistence[o] = walks ? k_i : -1;
         a.drop[o] = r_i;
         a.stability[o] = s_i;
         a.flags[o] = (uint8_t)fl;
       }
       if (a.layer_argmax && lane < a.K) {
         const long long ol = ((long long)lane * a.B + b) * a.L + i;
-        a.layer_argmax[ol] = my_y;
-        a.layer_conf[ol] = my_c;
-        a.layer_entropy[ol] = my_h;
+        const bool shown = lane >= a.K - seen;
+        a.layer_argmax[ol] = shown ? my_y : -1;
+        a.layer_conf[ol] = shown ? my_c : NAN;
+        a.layer_entropy[ol] = shown ? my_h : NAN;
       }
     }
   }
@@ -527,6 +515,7 @@ ScoreArgs score_args(const Launch& a) {
   s.layer_argmax = a.layer_argmax;
   s.layer_conf = a.layer_conf;
   s.layer_entropy = a.layer_entropy;
+  s.lazy = a.lazy_score ? (a.lazy_all ? 2 : 1) : 0;
   return s;
 }
 
@@ -552,11 +541,9 @@ CommitArgs commit_args(const Launch& a) {
 
 }  // namespace
 
-hipError_t launch_compact(const Launch& a, bool lazy_list, hipStream_t s) {
+hipError_t launch_compact(const Launch& a, bool lazy_list, int dtype, hipStream_t s) {
   FirstPassList fp{};
-  if (lazy_list)
-    fp = FirstPassList{a.lazy.act, a.lazy.rowoff, a.lazy.m, a.lazy.tier, (long long)(a.K - 1) * a.B * a.L, a.d,
-                       kStreamMaxRows, kBigTileRowsMid};
+  if (lazy_list) fp = FirstPassList{a.lazy, (long long)(a.K - 1) * a.B * a.L, a.K, a.d, lazy_classes(dtype)};
   hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, a.mask, a.B * a.L, a.max_masked, a.rows, a.n_masked,
                      a.dev_status, a.user_status, fp);
   return hipGetLastError();

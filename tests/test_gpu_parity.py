@@ -245,6 +245,44 @@ def test_lazy_projection_walking_every_position(name, ov, seed):
         assert np.abs(g["drop"][same] - eager["drop"][same]).max(initial=0.0) <= 2 * CONF_TOL
 
 
+# Lazy calls that walk in several passes (smaller ones are projected in one): matrices large enough that a pass is
+# worth fewer rows than the call has. bf16 passes of 1, then several layers a position; the rows of the later passes
+# fall in different size classes with the share of positions in the band; above 256 positions counts are read back.
+LAZY_PASS_CASES = [
+    ("band_few", dict(B=1, L=256, K=8, d=1024, V=20011, n_masked=250, sharp=("calibrated", -3.0, 1.0)), False, 71),
+    ("band_some", dict(B=1, L=256, K=8, d=1024, V=20011, n_masked=250, sharp=("calibrated", -1.0, 2.0)), False, 72),
+    ("every_position", dict(B=1, L=256, K=8, d=1024, V=20011, n_masked=250), False, 73),
+    ("read_back", dict(B=2, L=200, K=6, d=1024, V=20011, n_masked=190, sharp=("calibrated", -1.0, 2.0)), False, 74),
+    ("norm", dict(B=1, L=200, K=8, d=1000, V=20011, n_masked=190, sharp=("calibrated", -1.0, 2.0)), True, 75),
+    ("f32", dict(B=1, L=128, K=6, d=512, V=8009, n_masked=120, dtype="f32", sharp=("calibrated", -1.0, 2.0)), False, 76),
+    ("f32_norm_every_position", dict(B=2, L=80, K=6, d=514, V=8009, n_masked=70, dtype="f32"), True, 77),
+]
+
+
+@pytest.mark.parametrize("name,ov,norm,seed", LAZY_PASS_CASES, ids=[c[0] for c in LAZY_PASS_CASES])
+def test_lazy_passes(name, ov, norm, seed):
+    base = CONFIGS["llada_late"].with_(**{**dict(name="lazypass_" + name, masked_frac=None, sharp=("calibrated",),
+                                                 unstable_frac=0.25, layer_jitter=0.3), **ov})
+    w = make_workload(base, seed)
+    every = "every" in name
+    _check(w, dataclasses.replace(O.LLADA, lazy=True, lazy_all=every),
+           norm=(_gain(w, seed), 1e-5, False) if norm else None)
+
+
+@pytest.mark.parametrize("n", [3, 12])
+@pytest.mark.parametrize("K", [1, 4])
+def test_lazy_in_one_pass_reports_the_walk(n, K):
+    # few positions: all layers in one pass; per-layer outputs below the first disagreement stay unprojected
+    w = make_workload(CONFIGS["llada_late"].with_(name="lazyone", B=2, L=40, K=K, d=264, V=5003, n_masked=n,
+                                                  masked_frac=None, sharp=("calibrated",), unstable_frac=0.4), 80 + n)
+    for every in (False, True):
+        g, _, _ = _check(w, dataclasses.replace(O.LLADA, lazy=True, lazy_all=every))
+        m = w.mask != 0
+        depth = (g["layer_argmax"][:, m] >= 0).sum(0)
+        k = g["persistence"][m]
+        np.testing.assert_array_equal(depth, np.where(k < 0, 1, np.minimum(k + 1, K)))
+
+
 def test_lazy_projection_with_normalization_and_fp32():
     w = make_workload(CONFIGS["tiny"].with_(sharp=("calibrated",), unstable_frac=0.4), 8)
     _check(w, dataclasses.replace(O.LLADA, lazy=True), norm=(_gain(w, 3), 1e-6, False))
