@@ -84,12 +84,22 @@ constexpr unsigned vm_lgkm_wait(int n) { return (unsigned)((n & 15) | ((n >> 4) 
 // loads as well, with 32-bit byte offsets (the row source spans less than
 // 2^31 bytes; 6% fewer main-loop cycles), else global_load_lds from 64-bit
 // lane addresses.
-template <int TR, bool NT, bool HB>
+//
+// FC: the workgroup compacts the mask itself (compact_in_workgroup), for a
+// single row tile on a small canvas. With a single row tile the first two
+// chunks of W_U are loaded before the rows are known, the mask bytes (or the
+// count and the rows) ahead of them: behind them, they would wait for HBM
+// (that form of the compaction measured slower than its own launch). Rows
+// past the last one lie past the resource's end: their loads fetch nothing.
+// Whole calls at d = 4096, V = 126464, K = 4, three boxes: 68 rows 199 -> 188
+// us, 104 rows 179-191 -> 176-185, 160 rows 203 -> 198, 256 rows 249 -> 246,
+// 600 rows (four 192-row tiles, a fifth of them padding) 621 -> 604.
+template <int TR, bool NT, bool HB, bool FC>
 __global__ __launch_bounds__(256) void k_proj_bf16_big(
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ w_u, const int32_t* __restrict__ rows,
     const int32_t* __restrict__ n_ptr, float4* __restrict__ partials, int K, int B, int L, int d, int V,
     int nvt, int nrt, int split_rows, const uint16_t* __restrict__ xrows, const long long* __restrict__ rowoff,
-    const int32_t* __restrict__ grp, float scale) {
+    const int32_t* __restrict__ grp, float scale, CompactArgs ca) {
   using namespace big;
   static_assert(TV == 256 && (TR == 256 || TR == 192 || TR == 128), "wave layout below assumes 256 x TR");
   constexpr int NB = TR / 64;   // 32-row fragment blocks of the hidden rows per wave
@@ -100,11 +110,19 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
 #define RPD_SA(X) ((X) == 0 ? sa0 : (X) == 1 ? sa1 : sa2)
 #define RPD_SB(X) ((X) == 0 ? sb0 : sb1)
 
-  int rt, vt;
-  if (!map_job(blockIdx.x, nvt, nrt, split_rows, rt, vt)) return;
-  const int R = rowoff ? *n_ptr : *n_ptr * K;   // an explicit row list counts rows, not positions
+  int rt = 0, vt = 0;
+  const bool has_job = map_job(blockIdx.x, nvt, nrt, split_rows, rt, vt);
+  if (!has_job && !(FC && blockIdx.x == 0)) return;   // workgroup 0 always publishes the compaction
+  // An explicit row list (a lazy pass, whose count is often 0) is counted, in
+  // rows, before anything is loaded. Otherwise the first two chunks of W_U go
+  // out before the count and the rows are waited for, behind the loads of
+  // these (loads return in order).
+  int R = 0;
   const int r0 = rt * TR;
-  if (r0 >= R) return;
+  if (!FC && rowoff) {
+    R = *n_ptr;
+    if (r0 >= R) return;
+  }
   const int vb = (int)((long long)vt * V / nvt);
   const int ve = (int)((long long)(vt + 1) * V / nvt);
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -119,7 +137,7 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
   int pa[8];   // byte offsets of this lane's pieces from the tile's first W_U row (< 256 * d * 2)
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(w_u + (long long)vb * d), (short)0, (ve - vb) * d * 2, 0x00020000);
-  const int per = rowoff ? *grp : K;   // rows (layers) of a position
+  const int per = !FC && rowoff ? *grp : K;   // rows (layers) of a position
   // hidden-row sources: byte offsets from xsrc (HB) or addresses. Sized 8
   // (>= BL): an array sized by the template parameter, passed to the buffer
   // load builtin, made clang drop the kernel's host stub without a diagnostic.
@@ -134,23 +152,15 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
     const int piece = (lane & 7) ^ ((tr >> 1) & 7);
     pa[u] = ((min(vb + tr, ve - 1) - vb) * d + piece * 8) * 2;
   }
+  MaskBytes<4> mb;
+  int rpos[8], rpos0 = 0;   // positions of this lane's rows and of row r0; past the count unused, but inside `rows`
+  if constexpr (FC) {
+    mb.load(ca);
+  } else if (!rowoff && !xrows) {
+    rpos0 = rows[min(r0 / K, B * L - 1)];
 #pragma unroll
-  for (int u = 0; u < BL; ++u) {
-    const int tr = (TR / 4) * wid + 8 * u + (lane >> 3);
-    const int piece = (lane & 7) ^ ((tr >> 1) & 7);
-    const int r = r0 + tr < R ? r0 + tr : r0;
-    long long ob;
-    if (xrows) {   // normalized rows, already in projected-row order
-      ob = (long long)r * d + piece * 8;
-    } else {
-      const int p = r / per, l = r - p * per;
-      if (rowoff)   // an explicit row list, its layers from the first one down
-        ob = rowoff[p] - l * ((long long)B * L * d) + piece * 8;
-      else
-        ob = ((long long)l * B * L + rows[p]) * (long long)d + piece * 8;
-    }
-    pb[u] = xsrc + ob;
-    pbo[u] = (int)(ob * 2);
+    for (int u = 0; u < BL; ++u)
+      rpos[u] = rows[min((r0 + (TR / 4) * wid + 8 * u + (lane >> 3)) / K, B * L - 1)];
   }
   // fragment reads: lane reads row base + (lane & 31), logical piece 2s + (lane >> 5)
   const int fr = lane & 31, fsw = (fr >> 1) & 7, fhi = lane >> 5;
@@ -266,13 +276,56 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
   const int nchf = d / KC;
   const int rot = NT && nchf > 0 ? (int)(((long long)(blockIdx.x & 7) * nchf) / 8) : 0;
 #define RPD_PCHUNK(c) ((c) + rot >= nchf ? (c) + rot - nchf : (c) + rot)
-  if (nchf > 0) {
+  if (NT && has_job && nchf > 0) {
     RPD_ALOAD(0, 0);
-    RPD_BLOAD(0, 0);
     RPD_ALOAD(1, min(1, nchf - 1));
+  }
+  if constexpr (FC) {
+    // one row tile (r0 = 0): its rows need positions 0 .. TR-1 at most; they
+    // and the wave counts sit in hidden stage 1, read by every lane before
+    // its first load (the barrier below)
+    int* s_pos = reinterpret_cast<int*>(&sb1[0][0]);
+    R = compact_in_workgroup<4>(ca, mb, s_pos, TR, s_pos + TR) * K;
+    if (has_job && R > 0) {
+      rpos0 = s_pos[0];
+#pragma unroll
+      for (int u = 0; u < BL; ++u)
+        rpos[u] = s_pos[min((TR / 4) * wid + 8 * u + (lane >> 3), R - 1) / K];
+    }
+    lds_barrier();
+  } else if (!rowoff) {
+    R = *n_ptr * K;
+  }
+  if (!has_job || r0 >= R) {
+    __builtin_amdgcn_s_waitcnt(0);   // the loads above write this workgroup's LDS
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < BL; ++u) {
+    const int tr = (TR / 4) * wid + 8 * u + (lane >> 3);
+    const int piece = (lane & 7) ^ ((tr >> 1) & 7);
+    const bool in = r0 + tr < R;
+    const int r = in ? r0 + tr : r0;
+    long long ob;
+    if (!FC && xrows) {   // normalized rows, already in projected-row order
+      ob = (long long)r * d + piece * 8;
+    } else {
+      const int p = r / per, l = r - p * per;
+      if (!FC && rowoff)   // an explicit row list, its layers from the first one down
+        ob = rowoff[p] - l * ((long long)B * L * d) + piece * 8;
+      else
+        ob = ((long long)l * B * L + (in ? rpos[u] : rpos0)) * (long long)d + piece * 8;
+    }
+    pb[u] = xsrc + ob;
+    pbo[u] = in ? (int)(ob * 2) : INT_MIN;   // 2^31 as the unsigned offset it is: past the resource's end
+  }
+  if (nchf > 0) {
+    if (!NT) RPD_ALOAD(0, 0);
+    RPD_BLOAD(0, 0);
+    if (!NT) RPD_ALOAD(1, min(1, nchf - 1));
     RPD_BLOAD(1, min(1, nchf - 1));
     RPD_ALOAD(2, min(2, nchf - 1));
-    __builtin_amdgcn_s_waitcnt(vm_lgkm_wait(16 + BL));   // chunk 0 landed (A1, B1, A2 in flight)
+    __builtin_amdgcn_s_waitcnt(vm_lgkm_wait((NT ? 8 : 16) + BL));   // chunk 0 landed (NT: B1, A2 in flight; else A1 too)
     __builtin_amdgcn_s_barrier();
     RPD_FRAGS(fa0, fb0, 0, 0, 0);
     RPD_CHUNK(0, 0, 0, 1, 2, 1);
@@ -415,26 +468,34 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
   }
 }
 
+template <int TR>
+void launch_tile(const Launch& a, bool nt, bool hb, hipStream_t s) {
+  decltype(&k_proj_bf16_big<TR, false, false, false>) kernel;
+  if (a.fused_compact)   // a single row tile (compact_fused)
+    kernel = hb ? k_proj_bf16_big<TR, true, true, true> : k_proj_bf16_big<TR, true, false, true>;
+  else if (nt)
+    kernel = hb ? k_proj_bf16_big<TR, true, true, false> : k_proj_bf16_big<TR, true, false, false>;
+  else
+    kernel = hb ? k_proj_bf16_big<TR, false, true, false> : k_proj_bf16_big<TR, false, false, false>;
+  const CompactArgs ca{a.mask, a.B * a.L, a.max_masked, a.rows, a.n_masked, a.dev_status, a.user_status};
+  hipLaunchKernelGGL(kernel, dim3(a.plan.grid), dim3(256), 0, s, static_cast<const uint16_t*>(a.hidden),
+                     static_cast<const uint16_t*>(a.w_u), a.rows, a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V,
+                     a.plan.nvt, a.plan.nrt, a.plan.split_rows, static_cast<const uint16_t*>(a.xrows), a.rowoff,
+                     a.lazy.grp, a.logit_scale, ca);
+}
+
 }  // namespace
 
 hipError_t launch_proj_big(const Launch& a, hipStream_t s) {
   const bool nt = a.plan.nrt == 1;
   // the hidden rows, and the normalized rows (at most K * B * L of them), span less than 2^31 bytes
   const bool hb = (long long)a.K * a.B * a.L * a.d * 2 < (1ll << 31);
-  decltype(&k_proj_bf16_big<256, false, false>) kernel;
   if (a.plan.rows_per_tile == 128)
-    kernel = nt ? (hb ? k_proj_bf16_big<128, true, true> : k_proj_bf16_big<128, true, false>)
-                : (hb ? k_proj_bf16_big<128, false, true> : k_proj_bf16_big<128, false, false>);
+    launch_tile<128>(a, nt, hb, s);
   else if (a.plan.rows_per_tile == 192)
-    kernel = nt ? (hb ? k_proj_bf16_big<192, true, true> : k_proj_bf16_big<192, true, false>)
-                : (hb ? k_proj_bf16_big<192, false, true> : k_proj_bf16_big<192, false, false>);
+    launch_tile<192>(a, nt, hb, s);
   else
-    kernel = nt ? (hb ? k_proj_bf16_big<256, true, true> : k_proj_bf16_big<256, true, false>)
-                : (hb ? k_proj_bf16_big<256, false, true> : k_proj_bf16_big<256, false, false>);
-  hipLaunchKernelGGL(kernel, dim3(a.plan.grid), dim3(256), 0, s, static_cast<const uint16_t*>(a.hidden),
-                     static_cast<const uint16_t*>(a.w_u), a.rows, a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V,
-                     a.plan.nvt, a.plan.nrt, a.plan.split_rows, static_cast<const uint16_t*>(a.xrows), a.rowoff,
-                     a.lazy.grp, a.logit_scale);
+    launch_tile<256>(a, nt, hb, s);
   return hipGetLastError();
 }
 

@@ -6,55 +6,6 @@
 namespace rpd {
 namespace {
 
-// The masked-position compaction (K0) folded into the projection's
-// prologue, for small canvases: every workgroup scans the mask itself (while
-// its first W_U loads are in flight) and keeps the first `need` positions;
-// workgroup 0 also publishes the list, the count and the status for the
-// kernels that follow, exactly as k_compact does.
-struct CompactArgs {
-  const uint8_t* mask;
-  int BL, cap;
-  int32_t* rows;
-  int32_t* n;
-  int32_t* dev_status;
-  int32_t* user_status;
-};
-
-template <int NW>
-__device__ int compact_in_workgroup(const CompactArgs& ca, int* s_pos, int need, int* s_wave) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const bool publish = blockIdx.x == 0;
-  int carry = 0;
-  for (int base = 0; base < ca.BL; base += NW * 64) {
-    const int i = base + threadIdx.x;
-    const bool f = i < ca.BL && ca.mask[i] != 0;
-    const unsigned long long bal = __ballot(f);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) s_wave[wid] = __popcll(bal);
-    __syncthreads();
-    int off = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const int c = s_wave[w];
-      off += (w < wid) ? c : 0;
-      tot += c;
-    }
-    const int rank = carry + off + before;
-    if (f && rank < need) s_pos[rank] = i;
-    if (f && publish && rank < ca.cap) ca.rows[rank] = i;
-    carry += tot;
-    __syncthreads();
-  }
-  const int n = carry < ca.cap ? carry : ca.cap;
-  if (publish && threadIdx.x == 0) {
-    const int st = carry > ca.cap ? 1 : 0;
-    *ca.n = n;
-    *ca.dev_status = st;
-    if (ca.user_status) *ca.user_status = st;
-  }
-  return n;
-}
-
 // A workgroup of NW waves owns 32*MV*NW consecutive W_U rows (one
 // vocabulary tile) and all TR = 32*NB projected rows, over the full hidden
 // dimension, in 64-wide k-chunks.
@@ -146,7 +97,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
   // An explicit row list (a lazy pass) often has no rows at all, so its count
   // is read first (an empty launch then reads nothing: 1 us instead of 5).
   // Otherwise the W_U loads of the first two chunks go out before anything
-  // waits.
+  // waits (the mask bytes ahead of them, so that the scan does not wait for
+  // HBM, measured 0.4% slower at 32 rows).
   int R = 0, G = 1;   // G: layers taken of each listed position
   if (!FC && rowoff) {
     R = *n_ptr;
@@ -163,7 +115,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
   }
   if (FC) {
     // one row tile (r0 = 0): rows 0 .. TR-1 need positions 0 .. TR-1 at most
-    R = compact_in_workgroup<NW>(ca, s_pos, TR, s_wave) * K;
+    MaskBytes<NW> mb;
+    mb.load(ca);
+    R = compact_in_workgroup<NW>(ca, mb, s_pos, TR, s_wave) * K;
     if (!has_job) return;
   } else if (!rowoff) {
     R = *n_ptr * K;   // an explicit row list (above) counts rows, not positions
@@ -339,8 +293,8 @@ void launch_stream(const Launch& a, hipStream_t s) {
 
 bool compact_fused(const Launch& a) {
   const ProjVariant v = a.plan.variant;
-  const bool streaming = v == PROJ_BF16_S32 || v == PROJ_BF16_S64;
-  return streaming && a.plan.nrt == 1 && a.max_masked > 0 && (long long)a.B * a.L <= kFusedCompactMax &&
+  const bool bf16 = v != PROJ_F32;
+  return bf16 && a.plan.nrt == 1 && a.max_masked > 0 && (long long)a.B * a.L <= kFusedCompactMax &&
          !a.xrows && !a.rowoff;   // the normalization and explicit row lists need the compaction first
 }
 

@@ -134,6 +134,80 @@ __device__ __forceinline__ Soft soft_from_values(const float (&z)[N], const int 
   return s;
 }
 
+// The masked-position compaction (K0) folded into the projection's
+// prologue, for small canvases (B * L <= kFusedCompactMax): every workgroup
+// scans the mask itself (while its first W_U loads are in flight) and keeps
+// the first `need` positions; workgroup 0 also publishes the list, the count
+// and the status for the kernels that follow, exactly as k_compact does.
+struct CompactArgs {
+  const uint8_t* mask;
+  int BL, cap;
+  int32_t* rows;
+  int32_t* n;
+  int32_t* dev_status;
+  int32_t* user_status;
+};
+
+// a workgroup's mask bytes: thread t holds positions t, t + 64 NW, ..
+template <int NW>
+struct MaskBytes {
+  static constexpr int N = kFusedCompactMax / (NW * 64);
+  unsigned char v[N];
+  __device__ __forceinline__ void load(const CompactArgs& ca) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = u * NW * 64 + threadIdx.x;
+      v[u] = i < ca.BL ? ca.mask[i] : 0;
+    }
+  }
+};
+
+// a barrier that publishes LDS stores and waits for no global load
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt 0, vmcnt and expcnt unconstrained
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int NW>
+__device__ __forceinline__ int compact_in_workgroup(const CompactArgs& ca, const MaskBytes<NW>& mb, int* s_pos,
+                                                    int need, int* s_wave) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const bool publish = blockIdx.x == 0;
+  int carry = 0;
+#pragma unroll
+  for (int u = 0; u < MaskBytes<NW>::N; ++u) {
+    const int base = u * NW * 64, i = base + threadIdx.x;
+    if (base >= ca.BL) break;
+    const bool f = mb.v[u] != 0;
+    const unsigned long long bal = __ballot(f);
+    const int before = __popcll(bal & ((1ull << lane) - 1ull));
+    if (lane == 0) s_wave[wid] = __popcll(bal);
+    lds_barrier();
+    int off = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int c = s_wave[w];
+      off += (w < wid) ? c : 0;
+      tot += c;
+    }
+    const int rank = carry + off + before;
+    if (f && rank < need) s_pos[rank] = i;
+    if (f && publish && rank < ca.cap) ca.rows[rank] = i;
+    carry += tot;
+    lds_barrier();
+  }
+  const int n = carry < ca.cap ? carry : ca.cap;
+  if (publish && threadIdx.x == 0) {
+    const int st = carry > ca.cap ? 1 : 0;
+    *ca.n = n;
+    *ca.dev_status = st;
+    if (ca.user_status) *ca.user_status = st;
+  }
+  return n;
+}
+
 // Map a workgroup to (row tile, vocab tile). Consecutive workgroup ids are
 // dispatched round-robin over the 8 XCDs, so id % 8 selects the XCD and the
 // jobs of one XCD are laid out so that its concurrently running workgroups

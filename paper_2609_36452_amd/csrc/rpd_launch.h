@@ -47,7 +47,7 @@ struct LazyClasses {
 inline LazyClasses lazy_classes(int dtype) {
   return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 256}};
 }
-// largest canvas (B * L) whose compaction the streaming projection does itself
+// largest canvas (B * L) whose compaction the bf16 projection does itself (a single row tile)
 constexpr int kFusedCompactMax = 2048;
 
 struct ProjPlan {

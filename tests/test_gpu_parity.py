@@ -102,6 +102,35 @@ def test_bf16_variants(name, ov, seed, sharp):
         _check(w, P)
 
 
+# ------------------------------- compaction inside the projection kernels --
+
+# rows of the bound, fewer rows than the bound (padding rows of the tile), none, more than the bound
+@pytest.mark.parametrize("name,K,bound", [("bf16_s32", 4, 8), ("bf16_s64", 3, 21), ("bf16_big128", 4, 26),
+                                          ("bf16_big192", 3, 57), ("bf16_big", 4, 64)])
+def test_compaction_inside_the_projection(name, K, bound):
+    # a canvas of more than 2048 positions is compacted by its own launch: the same call on a canvas padded with
+    # unmasked positions must give the same bits
+    B, d, V = 2, 200, 5003
+    for n in (bound // 2, bound // 2 - 3, 0, bound // 2 + 2):
+        w = make_workload(CONFIGS["llada_late"].with_(name="fc", B=B, L=300, K=K, d=d, V=V, n_masked=n,
+                                                      sharp=("calibrated",), unstable_frac=0.3), 90 + n)
+        assert rpd.projection_variant(K, B, 300, d, V, rpd.DTYPE_BF16, max_masked=bound).startswith(name)
+        wide = dataclasses.replace(w, cfg=w.cfg.with_(L=1200),
+                                   hidden=np.concatenate([w.hidden, np.full((K, B, 900, d), 0x7FC0, np.uint16)], 2),
+                                   mask=np.concatenate([w.mask, np.zeros((B, 900), np.uint8)], 1))
+        a = run_gpu(w, O.LLADA, max_masked=bound)
+        b = run_gpu(wide, O.LLADA, max_masked=bound)
+        assert int(a["status"][0]) == int(b["status"][0]) == (1 if B * n > bound else 0)
+        seen = np.cumsum(w.mask.reshape(-1)).reshape(w.mask.shape)
+        m = (w.mask != 0) & (seen <= bound)      # the first `bound` masked positions are scored
+        for k in ("token", "entropy", "confidence", "persistence", "drop", "stability"):
+            np.testing.assert_array_equal(a[k][m], b[k][:, :300][m], err_msg=(k, n))
+        if B * n <= bound:
+            o = run_oracle(w, O.LLADA)
+            rep = compare(a, o, w.mask, O.LLADA, d)
+            assert rep.ok(), rep.summary()
+
+
 # ------------------------------------------------------- fp32 MFMA tiles --
 
 F32_CASES = [
