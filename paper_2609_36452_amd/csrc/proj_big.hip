@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
     // and the wave counts sit in hidden stage 1, read by every lane before
     // its first load (the barrier below)
     int* s_pos = reinterpret_cast<int*>(&sb1[0][0]);
-    R = compact_in_workgroup<4>(ca, mb, s_pos, TR, s_pos + TR) * K;
+    R = compact_in_workgroup<4>(ca, mb, s_pos, 0, TR, s_pos + TR) * K;
     if (has_job && R > 0) {
       rpos0 = s_pos[0];
 #pragma unroll

@@ -49,12 +49,17 @@ constexpr unsigned vm_lgkm_wait(int n) { return (unsigned)((n & 15) | ((n >> 4) 
 //
 // V16: 16-byte loads (d % 4 == 0 and 16-byte aligned sources); else 4-byte
 // loads, a quarter of the bytes per instruction.
-template <int WV, int NB, int NS, bool V16>
+//
+// FC: the workgroup compacts the mask itself (compact_in_workgroup), on a
+// small canvas: the first chunk of W_U is loaded while it
+// does, and the positions sit in the stage loaded last (from chunk 0's barrier
+// on).
+template <int WV, int NB, int NS, bool V16, bool FC>
 __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
     const float* __restrict__ hidden, const float* __restrict__ w_u, const int32_t* __restrict__ rows,
     const int32_t* __restrict__ n_ptr, float4* __restrict__ partials, int K, int B, int L, int d, int V, int nvt,
     int nrt, int split_rows, const float* __restrict__ xrows, const long long* __restrict__ rowoff,
-    const int32_t* __restrict__ grp, float scale) {
+    const int32_t* __restrict__ grp, float scale, CompactArgs ca) {
   constexpr int TV = 32 * WV, TR = 32 * NB, KC = 32;
   constexpr int RPI = V16 ? 8 : 2;             // rows per load instruction
   constexpr int AL = 32 / RPI;                 // W_U load instructions per wave per chunk
@@ -65,16 +70,44 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
 #define RPD_ST(X) ((X) == 0 ? st0 : (X) == 1 ? st1 : (X) == 2 ? st2 : st3)
   float4 (*red)[TR] = reinterpret_cast<float4 (*)[TR]>(&st0[0][0]);   // used after the loop only
 
-  int rt, vt;
-  if (!map_job(blockIdx.x, nvt, nrt, split_rows, rt, vt)) return;
-  const int R = rowoff ? *n_ptr : *n_ptr * K;   // an explicit row list counts rows, not positions
-  const int G = rowoff ? *grp : 1;   // and this many layers of each listed position
+  int rt = 0, vt = 0;
+  const bool has_job = map_job(blockIdx.x, nvt, nrt, split_rows, rt, vt);
+  if (!has_job && !(FC && blockIdx.x == 0)) return;   // workgroup 0 always publishes the compaction
   const int r0 = rt * TR;
-  if (r0 >= R) return;
+  int R = 0;
+  if (!FC) {
+    R = rowoff ? *n_ptr : *n_ptr * K;   // an explicit row list counts rows, not positions
+    if (r0 >= R) return;
+  }
+  const int per = !FC && rowoff ? *grp : K;   // rows (layers) of a position
   const int vb = (int)((long long)vt * V / nvt);
   const int ve = (int)((long long)(vt + 1) * V / nvt);
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
 
+#define RPD_FLOAD1(SRC, DST)                                                                               \
+  do { /* the builtin's size is a literal */                                                               \
+    if constexpr (V16)                                                                                     \
+      __builtin_amdgcn_global_load_lds((const void*)(SRC), (__attribute__((address_space(3))) void*)(DST), 16, 0, 0); \
+    else                                                                                                   \
+      __builtin_amdgcn_global_load_lds((const void*)(SRC), (__attribute__((address_space(3))) void*)(DST), 4, 0, 0);  \
+  } while (0)
+#define RPD_FLOADA(X, chunk)                                                                               \
+  do {                                                                                                     \
+    const long long k0_ = (long long)(chunk)*KC;                                                           \
+    _Pragma("unroll") for (int u_ = 0; u_ < AL; ++u_)                                                     \
+      RPD_FLOAD1(pa[u_] + k0_, &RPD_ST(X)[32 * wid + RPI * u_][0]);                                        \
+  } while (0)
+#define RPD_FLOADB(X, chunk)                                                                               \
+  do {                                                                                                     \
+    const long long k0_ = (long long)(chunk)*KC;                                                           \
+    _Pragma("unroll") for (int u_ = 0; u_ < BLD; ++u_)                                                    \
+      RPD_FLOAD1(pb[u_] + k0_, &RPD_ST(X)[TV + (TR / WV) * wid + RPI * u_][0]);                            \
+  } while (0)
+#define RPD_FLOAD(X, chunk)                                                                                \
+  do {                                                                                                     \
+    RPD_FLOADA(X, chunk);                                                                                  \
+    RPD_FLOADB(X, chunk);                                                                                  \
+  } while (0)
   // Load sources. Instruction u of this wave covers tile rows 32*wid + RPI*u
   // .. of W_U and (TR/WV)*wid + RPI*u .. of the hidden rows; the lane lands at
   // row + lane / (64/RPI), LDS float lk of the row, and fetches the global
@@ -90,21 +123,31 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
     ka[u] = (((lk >> 2) ^ ((tr >> 1) & 7)) << 2) + (lk & 3);
     pa[u] = w_u + (long long)min(vb + tr, ve - 1) * d + ka[u];
   }
+  const int nchf = d / KC;
+  int* s_pos = reinterpret_cast<int*>(&RPD_ST(NS - 1)[0][0]);   // the stage loaded last
+  if constexpr (FC) {
+    MaskBytes<WV> mb;
+    mb.load(ca);   // ahead of the loads below (loads return in order)
+    if (has_job && nchf > 0) RPD_FLOADA(0, 0);
+    R = compact_in_workgroup<WV>(ca, mb, s_pos, r0 / K, TR, s_pos + TR) * K;
+    if (!has_job || r0 >= R) {
+      __builtin_amdgcn_s_waitcnt(0);   // the loads above write this workgroup's LDS
+      return;
+    }
+  }
 #pragma unroll
   for (int u = 0; u < BLD; ++u) {
     const int tr = (TR / WV) * wid + RPI * u + lrow;
     kb[u] = (((lk >> 2) ^ ((tr >> 1) & 7)) << 2) + (lk & 3);
     const int r = r0 + tr < R ? r0 + tr : r0;
-    if (xrows) {   // normalized rows, already in projected-row order
+    if (!FC && xrows) {   // normalized rows, already in projected-row order
       pb[u] = xrows + (long long)r * d + kb[u];
-    } else if (rowoff) {   // an explicit row list
-      const int j = r / G;
-      pb[u] = hidden + rowoff[j] - (r - j * G) * ((long long)B * L * d) + kb[u];
     } else {
-      const int p = r / K, l = r - p * K;
-      const int pos = rows[p];
-      const int b = pos / L, i = pos - b * L;
-      pb[u] = hidden + (((long long)l * B + b) * L + i) * (long long)d + kb[u];
+      const int p = r / per, l = r - p * per;
+      if (!FC && rowoff)   // an explicit row list, its layers from the first one down
+        pb[u] = hidden + rowoff[p] - l * ((long long)B * L * d) + kb[u];
+      else
+        pb[u] = hidden + ((long long)l * B * L + (FC ? s_pos[p - r0 / K] : rows[p])) * (long long)d + kb[u];
     }
   }
   // fragment reads: row base + (lane & 31), logical piece 2s + (lane >> 5)
@@ -116,21 +159,6 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[nb][q] = 0.f;
 
-#define RPD_FLOAD1(SRC, DST)                                                                               \
-  do { /* the builtin's size is a literal */                                                               \
-    if constexpr (V16)                                                                                     \
-      __builtin_amdgcn_global_load_lds((const void*)(SRC), (__attribute__((address_space(3))) void*)(DST), 16, 0, 0); \
-    else                                                                                                   \
-      __builtin_amdgcn_global_load_lds((const void*)(SRC), (__attribute__((address_space(3))) void*)(DST), 4, 0, 0);  \
-  } while (0)
-#define RPD_FLOAD(X, chunk)                                                                                \
-  do {                                                                                                     \
-    const long long k0_ = (long long)(chunk)*KC;                                                           \
-    _Pragma("unroll") for (int u_ = 0; u_ < AL; ++u_)                                                     \
-      RPD_FLOAD1(pa[u_] + k0_, &RPD_ST(X)[32 * wid + RPI * u_][0]);                                        \
-    _Pragma("unroll") for (int u_ = 0; u_ < BLD; ++u_)                                                    \
-      RPD_FLOAD1(pb[u_] + k0_, &RPD_ST(X)[TV + (TR / WV) * wid + RPI * u_][0]);                            \
-  } while (0)
 #define RPD_FFRAG(F, X, S)                                                                                 \
   do {                                                                                                     \
     const int fc_ = 4 * ((2 * (S) + fhi) ^ fsw);                                                           \
@@ -165,9 +193,9 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
   } while (0)
 
   f32x4 f0[NB + 1], f1[NB + 1];   // a k-step's fragments: NB of hidden rows, then W_U's
-  const int nchf = d / KC;
   if (nchf > 0) {
-    RPD_FLOAD(0, 0);
+    if (!FC) RPD_FLOADA(0, 0);
+    RPD_FLOADB(0, 0);
     if constexpr (NS > 2) RPD_FLOAD(1, min(1, nchf - 1));
     if constexpr (NS > 3) RPD_FLOAD(2, min(2, nchf - 1));
     int c = 0;
@@ -211,6 +239,8 @@ __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
 #undef RPD_FMMA
 #undef RPD_FFRAG
 #undef RPD_FLOAD
+#undef RPD_FLOADA
+#undef RPD_FLOADB
 #undef RPD_FLOAD1
 #undef RPD_ST
 
@@ -249,11 +279,13 @@ void launch_f32(const Launch& a, hipStream_t s) {
   const ProjPlan& p = a.plan;
   const void* src = a.xrows ? a.xrows : a.hidden;
   const bool v16 = a.d % 4 == 0 && (((uintptr_t)src | (uintptr_t)a.w_u) & 15) == 0;
-  const auto kernel = v16 ? k_proj_f32<WV, NB, NS, true> : k_proj_f32<WV, NB, NS, false>;
+  const auto kernel = a.fused_compact ? (v16 ? k_proj_f32<WV, NB, NS, true, true> : k_proj_f32<WV, NB, NS, false, true>)
+                                      : (v16 ? k_proj_f32<WV, NB, NS, true, false> : k_proj_f32<WV, NB, NS, false, false>);
+  const CompactArgs ca{a.mask, a.B * a.L, a.max_masked, a.rows, a.n_masked, a.dev_status, a.user_status};
   hipLaunchKernelGGL(kernel, dim3(p.grid), dim3(WV * 64), 0, s, static_cast<const float*>(a.hidden),
                      static_cast<const float*>(a.w_u), a.rows, a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V, p.nvt,
                      p.nrt, p.split_rows, static_cast<const float*>(a.xrows), a.rowoff, a.lazy.grp,
-                     a.logit_scale);
+                     a.logit_scale, ca);
 }
 
 }  // namespace

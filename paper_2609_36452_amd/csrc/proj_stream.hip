@@ -117,7 +117,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
     // one row tile (r0 = 0): rows 0 .. TR-1 need positions 0 .. TR-1 at most
     MaskBytes<NW> mb;
     mb.load(ca);
-    R = compact_in_workgroup<NW>(ca, mb, s_pos, TR, s_wave) * K;
+    R = compact_in_workgroup<NW>(ca, mb, s_pos, 0, TR, s_wave) * K;
     if (!has_job) return;
   } else if (!rowoff) {
     R = *n_ptr * K;   // an explicit row list (above) counts rows, not positions
@@ -292,9 +292,11 @@ void launch_stream(const Launch& a, hipStream_t s) {
 }  // namespace
 
 bool compact_fused(const Launch& a) {
-  const ProjVariant v = a.plan.variant;
-  const bool bf16 = v != PROJ_F32;
-  return bf16 && a.plan.nrt == 1 && a.max_masked > 0 && (long long)a.B * a.L <= kFusedCompactMax &&
+  // fp32 tiles of several row tiles scan the mask too while it takes them a
+  // round or two (the bf16 ones are shorter and start later for it)
+  const bool f32 = a.plan.variant == PROJ_F32;
+  const long long most = a.plan.nrt == 1 ? kFusedCompactMax : (f32 ? kFusedCompactRowTiles : 0);
+  return a.max_masked > 0 && (long long)a.B * a.L <= most &&
          !a.xrows && !a.rowoff;   // the normalization and explicit row lists need the compaction first
 }
 

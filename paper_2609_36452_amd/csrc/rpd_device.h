@@ -137,8 +137,8 @@ __device__ __forceinline__ Soft soft_from_values(const float (&z)[N], const int 
 // The masked-position compaction (K0) folded into the projection's
 // prologue, for small canvases (B * L <= kFusedCompactMax): every workgroup
 // scans the mask itself (while its first W_U loads are in flight) and keeps
-// the first `need` positions; workgroup 0 also publishes the list, the count
-// and the status for the kernels that follow, exactly as k_compact does.
+// `need` positions from the p0-th on; workgroup 0 also publishes the list, the
+// count and the status for the kernels that follow, exactly as k_compact does.
 struct CompactArgs {
   const uint8_t* mask;
   int BL, cap;
@@ -172,7 +172,7 @@ __device__ __forceinline__ void lds_barrier() {
 
 template <int NW>
 __device__ __forceinline__ int compact_in_workgroup(const CompactArgs& ca, const MaskBytes<NW>& mb, int* s_pos,
-                                                    int need, int* s_wave) {
+                                                    int p0, int need, int* s_wave) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const bool publish = blockIdx.x == 0;
   int carry = 0;
@@ -193,7 +193,7 @@ __device__ __forceinline__ int compact_in_workgroup(const CompactArgs& ca, const
       tot += c;
     }
     const int rank = carry + off + before;
-    if (f && rank < need) s_pos[rank] = i;
+    if (f && rank >= p0 && rank - p0 < need) s_pos[rank - p0] = i;
     if (f && publish && rank < ca.cap) ca.rows[rank] = i;
     carry += tot;
     lds_barrier();

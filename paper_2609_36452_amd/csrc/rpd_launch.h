@@ -47,8 +47,10 @@ struct LazyClasses {
 inline LazyClasses lazy_classes(int dtype) {
   return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 256}};
 }
-// largest canvas (B * L) whose compaction the bf16 projection does itself (a single row tile)
+// largest canvas (B * L) whose compaction the projection does itself (with a single row tile)
 constexpr int kFusedCompactMax = 2048;
+// and with several, in fp32
+constexpr int kFusedCompactRowTiles = 512;
 
 struct ProjPlan {
   ProjVariant variant;

@@ -106,17 +106,19 @@ def test_bf16_variants(name, ov, seed, sharp):
 
 # rows of the bound, fewer rows than the bound (padding rows of the tile), none, more than the bound
 @pytest.mark.parametrize("name,K,bound", [("bf16_s32", 4, 8), ("bf16_s64", 3, 21), ("bf16_big128", 4, 26),
-                                          ("bf16_big192", 3, 57), ("bf16_big", 4, 64)])
+                                          ("bf16_big192", 3, 57), ("bf16_big", 4, 64), ("f32", 3, 42),
+                                          ("f32_small", 2, 16)])
 def test_compaction_inside_the_projection(name, K, bound):
     # a canvas of more than 2048 positions is compacted by its own launch: the same call on a canvas padded with
     # unmasked positions must give the same bits
-    B, d, V = 2, 200, 5003
+    B, d, V = 2, 200, 33003 if name == "f32" else 5003
+    dtype = "f32" if name.startswith("f32") else "bf16"
     for n in (bound // 2, bound // 2 - 3, 0, bound // 2 + 2):
-        w = make_workload(CONFIGS["llada_late"].with_(name="fc", B=B, L=300, K=K, d=d, V=V, n_masked=n,
+        w = make_workload(CONFIGS["llada_late"].with_(name="fc", B=B, L=300, K=K, d=d, V=V, n_masked=n, dtype=dtype,
                                                       sharp=("calibrated",), unstable_frac=0.3), 90 + n)
-        assert rpd.projection_variant(K, B, 300, d, V, rpd.DTYPE_BF16, max_masked=bound).startswith(name)
-        wide = dataclasses.replace(w, cfg=w.cfg.with_(L=1200),
-                                   hidden=np.concatenate([w.hidden, np.full((K, B, 900, d), 0x7FC0, np.uint16)], 2),
+        assert name.startswith(rpd.projection_variant(K, B, 300, d, V, int(dtype == "f32"), max_masked=bound))
+        nothing = np.full((K, B, 900, d), np.nan if dtype == "f32" else 0x7FC0, w.hidden.dtype)
+        wide = dataclasses.replace(w, cfg=w.cfg.with_(L=1200), hidden=np.concatenate([w.hidden, nothing], 2),
                                    mask=np.concatenate([w.mask, np.zeros((B, 900), np.uint8)], 1))
         a = run_gpu(w, O.LLADA, max_masked=bound)
         b = run_gpu(wide, O.LLADA, max_masked=bound)
