@@ -120,10 +120,22 @@ __device__ __forceinline__ Scored score_layers(const TY* y, const TF* c, const T
   o.h = h[(long long)(a.K - 1) * stride];
   int k_i = 1;
   float pk = o.c;
-  for (int l = a.K - 2; l >= 0; --l) {
-    if (y[(long long)l * stride] != o.y) break;
-    ++k_i;
-    pk = fmaxf(pk, c[(long long)l * stride]);
+  bool agree = true;
+  for (int l0 = a.K - 2; l0 >= 0 && agree; l0 -= 4) {   // four layers' loads in flight together
+    TY yl[4];
+    TF cl[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long long at = (long long)max(l0 - u, 0) * stride;
+      yl[u] = y[at];
+      cl[u] = c[at];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      agree = agree && l0 - u >= 0 && yl[u] == o.y;
+      k_i += agree ? 1 : 0;
+      pk = agree ? fmaxf(pk, cl[u]) : pk;
+    }
   }
   o.k = k_i;
   o.r = pk - o.c;
@@ -231,9 +243,37 @@ struct GlobalScores {
   const uint8_t* flags;
   const float* entropy;
   const float* confidence;
-  __device__ unsigned flag(long long o) const { return flags[o]; }
-  __device__ float ent(long long o) const { return entropy[o]; }
-  __device__ float conf(long long o) const { return confidence[o]; }
+  // loads issued together (entries of an unmasked position are read and ignored)
+  __device__ void get(long long o, bool, unsigned& fl, float& h, float& c) const {
+    fl = flags[o];
+    h = entropy[o];
+    c = confidence[o];
+  }
+};
+
+// Scoring from caller-supplied per-layer statistics as the commitment comes to
+// the position (score_layers; the flags are written with the commitment's).
+struct LayerScores {
+  const int32_t* l_y;
+  const float* l_c;
+  const float* l_h;
+  long long stride;
+  ScoreArgs a;
+  __device__ void get(long long o, bool masked, unsigned& fl, float& h, float& c) const {
+    fl = 0u;
+    h = c = 0.f;
+    if (!masked) return;
+    const Scored s = score_layers(l_y + o, l_c + o, l_h + o, stride, a);
+    a.token[o] = s.y;
+    a.entropy[o] = s.h;
+    a.confidence[o] = s.c;
+    a.persistence[o] = s.k;
+    a.drop[o] = s.r;
+    a.stability[o] = s.s;
+    fl = s.flags;
+    h = s.h;
+    c = s.c;
+  }
 };
 
 // The commitment of sequence b by the whole workgroup. N_i = entropy summed
@@ -281,11 +321,10 @@ __device__ __forceinline__ void commit_sequence(const uint8_t* __restrict__ mask
     const int i = c0 + threadIdx.x;
     const bool in = i < a.L;
     const long long o = base + i;
-    // loads issued together (entries of unmasked positions are read and ignored)
     const bool masked = in && mask[o] != 0;
-    const unsigned fl_in = in ? sc.flag(o) : 0u;
-    const float H_in = in ? sc.ent(o) : 0.f;
-    const float c_in = in ? sc.conf(o) : 0.f;
+    unsigned fl_in = 0u;
+    float H_in = 0.f, c_in = 0.f;
+    if (in) sc.get(o, masked, fl_in, H_in, c_in);
     const unsigned fl = masked ? fl_in : 0u;
     const bool cand = (fl & kFlagCandidate) != 0;
     const float H = masked ? H_in : 0.f;
@@ -369,6 +408,14 @@ __device__ __forceinline__ void commit_sequence(const uint8_t* __restrict__ mask
 // K3 alone: one workgroup per sequence, scoring results from the outputs
 __global__ __launch_bounds__(kCommitThreads) void k_commit(const uint8_t* __restrict__ mask, CommitArgs a) {
   commit_sequence(mask, a, blockIdx.x, GlobalScores{a.flags, a.entropy, a.confidence});
+}
+
+// Scoring and commitment from caller-supplied statistics, one workgroup per
+// sequence (one launch instead of two: the scoring alone took 3 us on the
+// stream, the gap between the two another 2).
+__global__ __launch_bounds__(kCommitThreads) void k_gate_commit(const uint8_t* __restrict__ mask, LayerScores sc,
+                                                                CommitArgs a) {
+  commit_sequence(mask, a, blockIdx.x, sc);
 }
 
 // K2: one workgroup of four waves per masked position. Wave w merges the
@@ -576,9 +623,18 @@ hipError_t launch_apply_commit(long long BL, uint8_t* mask, int32_t* canvas, con
   return hipGetLastError();
 }
 
+// longest sequence that one workgroup scores as it commits (two rounds of its
+// threads); longer ones are scored over the whole GPU first
+constexpr int kGateFusedMax = 2 * kCommitThreads;
+
 hipError_t launch_gate_commit(const Launch& a, const int32_t* l_y, const float* l_c, const float* l_h,
                               hipStream_t s) {
   const long long BL = (long long)a.B * a.L;
+  if (a.L <= kGateFusedMax) {
+    hipLaunchKernelGGL(k_gate_commit, dim3(a.B), dim3(commit_threads(a.L)), 0, s, a.mask,
+                       LayerScores{l_y, l_c, l_h, BL, score_args(a)}, commit_args(a));
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_gate_score, dim3((unsigned)((BL + 255) / 256)), dim3(256), 0, s, a.mask, l_y, l_c, l_h,
                      score_args(a));
   hipError_t e = hipGetLastError();

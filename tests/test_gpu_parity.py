@@ -560,6 +560,32 @@ def test_deterministic_bitwise():
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
 
 
+@pytest.mark.parametrize("K", [1, 4, 6])
+@pytest.mark.parametrize("L", [1, 700, 2048])
+def test_gate_commit_scores_as_it_commits(K, L):
+    # sequences of up to 2048 positions are scored by the workgroup that commits them, longer ones before it: the
+    # same statistics on a canvas padded with unmasked positions must give the same bits
+    rng = np.random.default_rng(K * L)
+    B, wide = 2, 2049 + L
+    mask = (rng.random((B, L)) < 0.6).astype(np.uint8)
+    y = rng.integers(0, 2, size=(K, B, L)).astype(np.int32)
+    conf = rng.uniform(0.3, 1.0, size=(K, B, L)).astype(np.float32)
+    conf[:, 0, : min(L, 3)] = np.nan
+    ent = rng.exponential(0.02, size=(K, B, L)).astype(np.float32)
+    pad = lambda a: np.concatenate([a, np.zeros(a.shape[:-1] + (wide - L,), a.dtype)], -1)
+    P = gpu_params(O.Params(theta_s=2.5, w=5.0, beta=3.0, block=32 if L == 700 else 0))
+    res = []
+    for arrays in ((mask, y, conf, ent), tuple(pad(a) for a in (mask, y, conf, ent))):
+        g = rpd.gate_commit(*[torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in arrays], P)
+        torch.cuda.synchronize()
+        res.append({k: v.cpu().numpy() for k, v in g.items() if k != "status"})
+    for k in res[0]:
+        a, b = res[0][k], res[1][k]
+        np.testing.assert_array_equal(a, b if b.ndim == 1 else b[:, :L], err_msg=k)
+        if b.ndim == 2:
+            assert (b[:, L:] == (-1 if k == "token" else 0)).all(), k
+
+
 @pytest.mark.parametrize("block", [0, 32, 5])
 def test_gate_commit_matches_oracle_selection(block):
     rng = np.random.default_rng(3)
