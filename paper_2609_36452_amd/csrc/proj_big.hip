@@ -471,7 +471,7 @@ __global__ __launch_bounds__(256) void k_proj_bf16_big(
 template <int TR>
 void launch_tile(const Launch& a, bool nt, bool hb, hipStream_t s) {
   decltype(&k_proj_bf16_big<TR, false, false, false>) kernel;
-  if (a.fused_compact)   // a single row tile (compact_fused)
+  if (a.fused_compact && !a.xrows)   // a single row tile (compact_fused)
     kernel = hb ? k_proj_bf16_big<TR, true, true, true> : k_proj_bf16_big<TR, true, false, true>;
   else if (nt)
     kernel = hb ? k_proj_bf16_big<TR, true, true, false> : k_proj_bf16_big<TR, true, false, false>;

@@ -279,7 +279,7 @@ void launch_f32(const Launch& a, hipStream_t s) {
   const ProjPlan& p = a.plan;
   const void* src = a.xrows ? a.xrows : a.hidden;
   const bool v16 = a.d % 4 == 0 && (((uintptr_t)src | (uintptr_t)a.w_u) & 15) == 0;
-  const auto kernel = a.fused_compact ? (v16 ? k_proj_f32<WV, NB, NS, true, true> : k_proj_f32<WV, NB, NS, false, true>)
+  const auto kernel = a.fused_compact && !a.xrows ? (v16 ? k_proj_f32<WV, NB, NS, true, true> : k_proj_f32<WV, NB, NS, false, true>)
                                       : (v16 ? k_proj_f32<WV, NB, NS, true, false> : k_proj_f32<WV, NB, NS, false, false>);
   const CompactArgs ca{a.mask, a.B * a.L, a.max_masked, a.rows, a.n_masked, a.dev_status, a.user_status};
   hipLaunchKernelGGL(kernel, dim3(p.grid), dim3(WV * 64), 0, s, static_cast<const float*>(a.hidden),

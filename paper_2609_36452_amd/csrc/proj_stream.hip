@@ -275,7 +275,7 @@ void launch_stream(const Launch& a, hipStream_t s) {
   static_assert(32 * MV * NW == kStreamTileVocab, "every streaming variant covers the same vocabulary tile");
   const ProjPlan& p = a.plan;
   const CompactArgs ca{a.mask, a.B * a.L, a.max_masked, a.rows, a.n_masked, a.dev_status, a.user_status};
-  if (a.fused_compact)
+  if (a.fused_compact && !a.xrows)
     hipLaunchKernelGGL((k_proj_bf16_stream<NW, MV, NB, true>), dim3(p.grid), dim3(NW * 64), 0, s,
                        static_cast<const uint16_t*>(a.hidden), static_cast<const uint16_t*>(a.w_u), a.rows,
                        a.n_masked, a.partials, a.K, a.B, a.L, a.d, a.V, p.nvt, p.nrt, p.split_rows, ca,
@@ -292,12 +292,15 @@ void launch_stream(const Launch& a, hipStream_t s) {
 }  // namespace
 
 bool compact_fused(const Launch& a) {
-  // fp32 tiles of several row tiles scan the mask too while it takes them a
-  // round or two (the bf16 ones are shorter and start later for it)
+  if (a.max_masked <= 0 || a.rowoff) return false;   // an explicit row list is listed by the compaction
+  // the normalization comes first (a canvas of 2000 positions: 0.7 us longer
+  // than with the launch); fp32 tiles of several row tiles scan the
+  // mask while it takes them a round or two (the bf16 ones are shorter and
+  // start later for it)
   const bool f32 = a.plan.variant == PROJ_F32;
-  const long long most = a.plan.nrt == 1 ? kFusedCompactMax : (f32 ? kFusedCompactRowTiles : 0);
-  return a.max_masked > 0 && (long long)a.B * a.L <= most &&
-         !a.xrows && !a.rowoff;   // the normalization and explicit row lists need the compaction first
+  const long long most = a.xrows ? kFusedCompactTwoRounds
+                                 : (a.plan.nrt == 1 ? kFusedCompactMax : (f32 ? kFusedCompactTwoRounds : 0));
+  return (long long)a.B * a.L <= most;
 }
 
 hipError_t launch_proj_stream(const Launch& a, hipStream_t s) {

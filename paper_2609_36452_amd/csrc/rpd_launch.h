@@ -47,10 +47,10 @@ struct LazyClasses {
 inline LazyClasses lazy_classes(int dtype) {
   return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 256}};
 }
-// largest canvas (B * L) whose compaction the projection does itself (with a single row tile)
+// largest canvas (B * L) whose compaction the projection does itself with a single row tile
 constexpr int kFusedCompactMax = 2048;
-// and with several, in fp32
-constexpr int kFusedCompactRowTiles = 512;
+// and with several, in fp32, or the normalization does
+constexpr int kFusedCompactTwoRounds = 512;
 
 struct ProjPlan {
   ProjVariant variant;
@@ -128,7 +128,7 @@ struct Launch {
   // workspace pieces
   int32_t* n_masked;     // [1] device count (clamped to max_masked)
   int32_t* dev_status;   // [1] internal status word
-  bool fused_compact;    // the projection kernel does the compaction (no launch_compact)
+  bool fused_compact;    // the normalization, or without one the projection, does the compaction (no launch_compact)
   int32_t* rows;         // [max_masked] compacted b*L+i
   float4* partials;      // [K*max_masked][nvt]
   // final normalization (norm_weight NULL: none): the projection then reads
@@ -176,7 +176,7 @@ hipError_t launch_lazy_next(const Launch& a, int dtype, int min_group, int pass_
 // classes, when the pass ran once per class (NULL: a.plan)
 hipError_t launch_lazy_reduce(const Launch& a, int dtype, int m_cap, const ProjPlan* class_plans, hipStream_t s);
 hipError_t launch_lazy_score(const Launch& a, hipStream_t s);
-// the projection does the compaction itself (needs a.plan and a.max_masked
+// the projection or the normalization does the compaction itself (needs a.plan and a.max_masked
 // >= 0): the call then launches no compaction kernel
 bool compact_fused(const Launch& a);
 

@@ -219,6 +219,18 @@ def test_logit_scale(name, scale):
     _check(w, dataclasses.replace(O.DREAM, logit_scale=scale))
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 8), ("bf16", 2040), ("bf16", 2048), ("bf16", 8200), ("f32", 13),
+                                     ("f32", 1024), ("f32", 1026), ("f32", 4100)])
+@pytest.mark.parametrize("L", [60, 600])
+def test_normalization_row_lengths(dtype, d, L):
+    # rows shorter than a workgroup's loads, pieces of 1, 2, 4 and 8 elements, longer than what its registers keep;
+    # the compaction inside (60 positions) and before it (600)
+    w = make_workload(CONFIGS["llada_late"].with_(name="norm_rows", B=1, L=L, K=3, d=d, V=1500, n_masked=9, dtype=dtype,
+                                                  masked_frac=None, sharp=("calibrated",), unstable_frac=0.3), d)
+    _check(w, O.LLADA, norm=(_gain(w, d), 1e-5, False))
+    _check(w, O.LLADA, norm=(_gain(w, d), 1e-5, True), max_masked=12)
+
+
 def test_fp32_normalization_and_scale():
     w = make_workload("tiny", 7)
     norm = (_gain(w, 9), 1e-6, False)
