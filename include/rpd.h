@@ -15,7 +15,10 @@
  * Conventions for every entry point:
  *  - Pointers marked "device" are HIP device (or managed) memory on the
  *    current device; "host" pointers are read during the call only.
- *  - The caller owns every buffer. The library allocates no device memory,
+ *  - The caller owns every buffer. The library allocates no device memory (a
+ *    call that waits for a count has it stored in one page of pinned host
+ *    memory, allocated by the process's first such call; rpd_score_commit_noalloc
+ *    never uses it),
  *    keeps no pointer after it returns, and never writes its inputs.
  *  - Work is enqueued asynchronously on `stream` (a hipStream_t; NULL = the
  *    default stream). Results are valid once the stream has completed.
@@ -101,8 +104,8 @@ typedef enum rpd_status {
  *   norm_final  0: layer K-1 is the model's native normalized state (the
  *               paper); 1: normalize it like the others
  *   max_masked  an upper bound on the number of masked positions summed over
- *               the batch, or -1. With -1 the call reads the exact count back
- *               from the device once (one stream synchronisation). If the
+ *               the batch, or -1. With -1 the call waits once for the exact
+ *               count (and so for the work on the stream before it). If the
  *               bound is exceeded, only the first max_masked masked positions
  *               (batch-major, canvas order) are scored, the results for the
  *               rest are undefined, and RPD_DEVICE_STATUS_MASKED_OVERFLOW is

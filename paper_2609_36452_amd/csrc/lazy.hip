@@ -128,7 +128,8 @@ __global__ __launch_bounds__(64 * kLazyReduceWaves) void k_lazy_reduce(
 constexpr int kLazyNextThreads = 1024;
 __global__ __launch_bounds__(kLazyNextThreads) void k_lazy_next(const int32_t* __restrict__ n_ptr, LazyState st,
                                                                 const int32_t* __restrict__ rows, int cap, int B, int L,
-                                                                int d, int min_group, int pass_rows, LazyClasses cls) {
+                                                                int d, int min_group, int pass_rows, LazyClasses cls,
+                                                                int32_t* host_m) {
   __shared__ int wsum[kLazyNextThreads / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
   // the first chunk's state and row are loaded with the counts (p < cap stays
@@ -168,6 +169,7 @@ __global__ __launch_bounds__(kLazyNextThreads) void k_lazy_next(const int32_t* _
     // with no position alive the pass is empty and the walk over: the layer
     // stays where it is, so that later passes find nothing either
     const int g = lazy_group(carry, l + 1, min_group, pass_rows);
+    if (host_m) __hip_atomic_store(host_m, g > 0 ? carry : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     list_pass(st, g > 0 ? carry : 0, g > 0 ? g : 1, g > 0 ? l : 0, cls);
   }
 }
@@ -211,9 +213,9 @@ __global__ __launch_bounds__(256) void k_lazy_score(const int32_t* __restrict__ 
 
 }  // namespace
 
-hipError_t launch_lazy_next(const Launch& a, int dtype, int min_group, int pass_rows, hipStream_t s) {
+hipError_t launch_lazy_next(const Launch& a, int dtype, int min_group, int pass_rows, int32_t* host_m, hipStream_t s) {
   hipLaunchKernelGGL(k_lazy_next, dim3(1), dim3(kLazyNextThreads), 0, s, a.n_masked, a.lazy, a.rows, a.max_masked, a.B,
-                     a.L, a.d, min_group, pass_rows, lazy_classes(dtype));
+                     a.L, a.d, min_group, pass_rows, lazy_classes(dtype), host_m);
   return hipGetLastError();
 }
 

@@ -2,6 +2,8 @@
 // launch planning and error reporting. Kernels live in proj_*.hip and
 // score_commit.hip; the projection plan in proj_plan.cpp.
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -135,12 +137,88 @@ void fill_common(rpd::Launch& a, const rpd_params* q, const rpd_outputs* o) {
   a.user_status = o->status;
 }
 
+// A count that the host waits for comes through pinned host memory: the kernel
+// that has it stores it there (system scope) and the host polls the slot. A
+// device-to-host copy and a stream synchronisation in its place left the GPU
+// idle for 39 us between the compaction and the projection, 10-17 us longer
+// (calls that read the count back, d = 4096, V = 126464: 32 rows 186.9 ->
+// 173.5 us, 256 rows 265 -> 257; lazy over 800 positions at d = 2000, V =
+// 30000: 623 -> 559). The slots are one page for the whole process, allocated on first use
+// and kept; a call takes one and gives it back, and one that finds none (or
+// may not allocate, or is under capture) copies the count as before.
+constexpr int kSlots = 64;
+std::atomic<uint64_t> g_slots_free{~0ull};
+std::once_flag g_slots_once;
+struct alignas(64) Slot {
+  int32_t count;
+};
+Slot* g_slots = nullptr;
+
+class CountSlot {
+ public:
+  CountSlot(bool allowed, hipStream_t s) {
+    if (!allowed) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+    std::call_once(g_slots_once, [] {
+      // allowed also while another thread captures a graph
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, sizeof(Slot) * kSlots, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess)
+        g_slots = static_cast<Slot*>(p);
+      (void)hipThreadExchangeStreamCaptureMode(&mode);
+    });
+    if (!g_slots) return;
+    uint64_t f = g_slots_free.load(std::memory_order_relaxed);
+    while (f && !g_slots_free.compare_exchange_weak(f, f & (f - 1), std::memory_order_acquire)) {
+    }
+    if (f) index_ = __builtin_ctzll(f);
+  }
+  ~CountSlot() {
+    if (index_ >= 0) g_slots_free.fetch_or(1ull << index_, std::memory_order_release);
+  }
+  CountSlot(const CountSlot&) = delete;
+  CountSlot& operator=(const CountSlot&) = delete;
+
+  // where the next kernel is to store the count; NULL: it is copied from the device
+  int32_t* arm() {
+    if (index_ < 0) return nullptr;
+    __atomic_store_n(&g_slots[index_].count, -1, __ATOMIC_RELEASE);
+    return &g_slots[index_].count;
+  }
+  // the count that a kernel on s armed above stores, or has at `dev`
+  hipError_t wait(const int32_t* dev, hipStream_t s, int32_t* out) {
+    if (index_ >= 0) {
+      const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+      for (int k = 1;; ++k) {
+        *out = __atomic_load_n(&g_slots[index_].count, __ATOMIC_ACQUIRE);
+        if (*out >= 0) return hipSuccess;
+        __builtin_ia32_pause();
+        if (k % 64 == 0 && std::chrono::steady_clock::now() > end) break;
+      }
+      // much work before it on the stream (or a kernel that will not run): wait without polling
+      const hipError_t e = hipStreamSynchronize(s);
+      if (e == hipSuccess) *out = __atomic_load_n(&g_slots[index_].count, __ATOMIC_ACQUIRE);
+      if (e == hipSuccess && *out >= 0) return hipSuccess;
+      index_ = -1;   // not given back: a kernel may yet store to it
+      return e == hipSuccess ? hipErrorUnknown : e;
+    }
+    hipError_t e = hipMemcpyAsync(out, dev, sizeof *out, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    return e;
+  }
+
+ private:
+  int index_ = -1;
+};
+
 // Lazy layerwise projection: projection passes from the final layer down over
 // the positions still walking their agreement suffix, each over as many
 // layers of them as lazy_group gives (rows listed by k_lazy_next); how a pass
 // is planned for a count that only the device knows is described in the loop.
 template <class Mark>
-hipError_t run_lazy(rpd::Launch& a, int dtype, hipStream_t s, Mark& mark) {
+hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, Mark& mark) {
   hipError_t e = mark(1);
   if (e != hipSuccess) return e;
   if (a.max_masked > 0) {
@@ -173,12 +251,12 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, hipStream_t s, Mark& mark) {
     for (int t = 0;; ++t) {
       long long rows_cap = m_host;
       if (t > 0) {
-        if ((e = rpd::launch_lazy_next(a, dtype, min_group, pass_rows, s)) != hipSuccess) return e;
         known = m_host > rpd::kLazyGateRows;
+        if ((e = rpd::launch_lazy_next(a, dtype, min_group, pass_rows, known ? slot.arm() : nullptr, s)) != hipSuccess)
+          return e;
         if (known) {
           int32_t m = 0;
-          if ((e = hipMemcpyAsync(&m, a.lazy.m, sizeof m, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-          if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+          if ((e = slot.wait(a.lazy.m, s, &m)) != hipSuccess) return e;
           if (m <= 0) break;
           m_host = m;
         }
@@ -267,7 +345,7 @@ int32_t rpd_projection_variant(const rpd_problem* p) {
 
 static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, const rpd_outputs* o,
                                     void* workspace, size_t workspace_bytes, void* stream, void* const* events,
-                                    int32_t n_events) {
+                                    int32_t n_events, bool may_pin) {
   g_err[0] = '\0';
   if (!p) return fail(RPD_ERR_NULL_POINTER, "problem is NULL");
   if (!p->hidden || !p->w_u || !p->mask) return fail(RPD_ERR_NULL_POINTER, "hidden, w_u and mask are required");
@@ -366,12 +444,13 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
     a.fused_compact = !lazy && rpd::compact_fused(a);
   }
   hipError_t e = mark(0);
-  if (e == hipSuccess && !a.fused_compact) e = rpd::launch_compact(a, lazy, p->dtype, s);
+  CountSlot slot(may_pin && (p->max_masked < 0 || (lazy && cap > rpd::kLazyGateRows)), s);
+  if (e == hipSuccess && !a.fused_compact)
+    e = rpd::launch_compact(a, lazy, p->dtype, p->max_masked < 0 ? slot.arm() : nullptr, s);
   if (e != hipSuccess) return fail(RPD_ERR_HIP, "compaction: %s", hipGetErrorString(e));
   if (p->max_masked < 0) {
     int32_t n = 0;
-    e = hipMemcpyAsync(&n, a.n_masked, sizeof n, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    e = slot.wait(a.n_masked, s, &n);
     if (e != hipSuccess) return fail(RPD_ERR_HIP, "reading the masked count: %s", hipGetErrorString(e));
     a.max_masked = n;
     a.plan = rpd::plan_projection(p->dtype, (long long)p->K * a.max_masked, p->V);
@@ -379,7 +458,7 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
   }
   a.lazy_score = lazy_call && !lazy;
   if (lazy) {
-    e = run_lazy(a, p->dtype, s, mark);
+    e = run_lazy(a, p->dtype, slot, s, mark);
   } else if ((e = mark(1)) == hipSuccess && (!a.xrows || (e = rpd::launch_norm_rows(a, s)) == hipSuccess) &&
              (e = rpd::launch_projection(a, s)) == hipSuccess && (e = mark(2)) == hipSuccess &&
              (e = rpd::launch_reduce_score(a, s)) == hipSuccess && (e = mark(3)) == hipSuccess &&
@@ -392,13 +471,13 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
 
 rpd_status rpd_score_commit(const rpd_problem* p, const rpd_params* q, const rpd_outputs* o, void* workspace,
                             size_t workspace_bytes, void* stream) {
-  return score_commit_impl(p, q, o, workspace, workspace_bytes, stream, nullptr, 0);
+  return score_commit_impl(p, q, o, workspace, workspace_bytes, stream, nullptr, 0, true);
 }
 
 rpd_status rpd_score_commit_timed(const rpd_problem* p, const rpd_params* q, const rpd_outputs* o,
                                   void* workspace, size_t workspace_bytes, void* stream, void* const* events,
                                   int32_t n_events) {
-  return score_commit_impl(p, q, o, workspace, workspace_bytes, stream, events, n_events);
+  return score_commit_impl(p, q, o, workspace, workspace_bytes, stream, events, n_events, true);
 }
 
 rpd_status rpd_score_commit_noalloc(const rpd_problem* p, const rpd_params* q, const rpd_outputs* o,
@@ -418,7 +497,7 @@ rpd_status rpd_score_commit_noalloc(const rpd_problem* p, const rpd_params* q, c
     const hipError_t e = scratch_address(&ws);
     if (e != hipSuccess) return fail(RPD_ERR_HIP, "looking up the scratch array: %s", hipGetErrorString(e));
   }
-  return score_commit_impl(p, q, o, ws, RPD_NOALLOC_SCRATCH_BYTES, stream, nullptr, 0);
+  return score_commit_impl(p, q, o, ws, RPD_NOALLOC_SCRATCH_BYTES, stream, nullptr, 0, false);   // allocates nothing
 }
 
 rpd_status rpd_apply_commit(int32_t B, int32_t L, uint8_t* mask, int32_t* canvas, const uint8_t* commit,

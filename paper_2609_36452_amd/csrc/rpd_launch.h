@@ -163,7 +163,8 @@ struct Launch {
 // enqueue, in this order: compaction, projection, reduction + scoring,
 // commitment (the last three use a.plan and a.max_masked)
 // lazy_list: also list the first lazy pass (a.lazy), of type dtype
-hipError_t launch_compact(const Launch& a, bool lazy_list, int dtype, hipStream_t s);
+// host_n: host memory to store the count in as well (or NULL)
+hipError_t launch_compact(const Launch& a, bool lazy_list, int dtype, int32_t* host_n, hipStream_t s);
 hipError_t launch_projection(const Launch& a, hipStream_t s);
 hipError_t launch_reduce_score(const Launch& a, hipStream_t s);
 hipError_t launch_commit(const Launch& a, hipStream_t s);
@@ -171,7 +172,8 @@ hipError_t launch_commit(const Launch& a, hipStream_t s);
 // lazy layerwise projection: list the next pass (the positions still walking
 // and the layers it takes of each, lazy_group), reduce a pass, score from the
 // per-position state
-hipError_t launch_lazy_next(const Launch& a, int dtype, int min_group, int pass_rows, hipStream_t s);
+// (host_m: host memory to store the positions' count in as well, or NULL)
+hipError_t launch_lazy_next(const Launch& a, int dtype, int min_group, int pass_rows, int32_t* host_m, hipStream_t s);
 // m_cap: bound on the pass's positions; class_plans: the plans of the size
 // classes, when the pass ran once per class (NULL: a.plan)
 hipError_t launch_lazy_reduce(const Launch& a, int dtype, int m_cap, const ProjPlan* class_plans, hipStream_t s);

@@ -23,7 +23,8 @@ struct FirstPassList {
 __global__ __launch_bounds__(1024) void k_compact(const uint8_t* __restrict__ mask, int BL, int cap,
                                                    int32_t* __restrict__ rows, int32_t* __restrict__ n_out,
                                                    int32_t* __restrict__ dev_status,
-                                                   int32_t* __restrict__ user_status, FirstPassList fp) {
+                                                   int32_t* __restrict__ user_status, int32_t* host_n,
+                                                   FirstPassList fp) {
   __shared__ int wsum[16];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
   int carry = 0;
@@ -60,6 +61,7 @@ __global__ __launch_bounds__(1024) void k_compact(const uint8_t* __restrict__ ma
     *n_out = n;
     *dev_status = st;
     if (user_status) *user_status = st;
+    if (host_n) __hip_atomic_store(host_n, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (fp.st.act) list_pass(fp.st, n, 1, fp.K - 1, fp.cls);
   }
 }
@@ -588,11 +590,11 @@ CommitArgs commit_args(const Launch& a) {
 
 }  // namespace
 
-hipError_t launch_compact(const Launch& a, bool lazy_list, int dtype, hipStream_t s) {
+hipError_t launch_compact(const Launch& a, bool lazy_list, int dtype, int32_t* host_n, hipStream_t s) {
   FirstPassList fp{};
   if (lazy_list) fp = FirstPassList{a.lazy, (long long)(a.K - 1) * a.B * a.L, a.K, a.d, lazy_classes(dtype)};
   hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, a.mask, a.B * a.L, a.max_masked, a.rows, a.n_masked,
-                     a.dev_status, a.user_status, fp);
+                     a.dev_status, a.user_status, host_n, fp);
   return hipGetLastError();
 }
 

@@ -572,6 +572,36 @@ def test_deterministic_bitwise():
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
 
 
+def test_counts_read_back_by_several_threads():
+    # calls that wait for the masked count, from threads with streams of their own, twice as many as there are
+    # distinct problems; each gets its own count (the plan and the results depend on it)
+    import threading
+    ws = [make_workload(CONFIGS["llada_late"].with_(name="thr", B=1, L=160, K=4, d=136, V=3001, n_masked=n,
+                                                    sharp=("calibrated",), unstable_frac=0.3), n)
+          for n in (0, 5, 16, 40, 100, 160)]
+    args = [to_device(w) for w in ws]
+    ref = [run_gpu(w, O.LLADA, layer_stats=False, tensors=t) for w, t in zip(ws, args)]
+    streams = [torch.cuda.Stream() for _ in range(2 * len(ws))]
+    bad = []
+
+    def work(j):
+        t, r = args[j % len(ws)], ref[j % len(ws)]
+        with torch.cuda.stream(streams[j]):
+            for _ in range(20):
+                o = rpd.score_commit(*t, gpu_params(O.LLADA))
+                streams[j].synchronize()
+                if not all(np.array_equal(o[k].cpu().numpy(), r[k]) for k in ("token", "entropy", "flags", "n_commit")):
+                    bad.append(j)
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(j,)) for j in range(len(streams))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+
+
 @pytest.mark.parametrize("K", [1, 4, 6])
 @pytest.mark.parametrize("L", [1, 700, 2048])
 def test_gate_commit_scores_as_it_commits(K, L):
