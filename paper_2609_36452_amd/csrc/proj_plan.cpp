@@ -68,7 +68,7 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
 // in fp32), whichever is more. kPassUs: what a pass costs besides, its
 // launches (up to four projections of which one runs, reduction, listing:
 // about 5 us each on the stream).
-static constexpr double kPassUs = 25.0;
+static constexpr double kPassUs = 30.0;
 static double stream_us(int dtype, int d, int V) { return (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / 6.7e6); }
 static double row_us(int dtype, int d, int V) { return 2.0 * V * d / (dtype == 1 ? 128e6 : 1050e6); }
 
@@ -77,17 +77,34 @@ int lazy_pass_rows(int dtype, int d, int V) {
   return r < 1.0 ? 1 : (r > 1e6 ? 1000000 : (int)r);
 }
 
+// A pass over `rows` rows: in bf16 above the ridge an affine fit (at d = 4096,
+// V = 126464: 244 us at 256 rows, 440 at 512, 600 at 768, 815 at 1024).
+static double pass_us(int dtype, double rows, int d, int V) {
+  const double st = stream_us(dtype, d, V);
+  if (dtype == 1) return std::max(st, rows * row_us(dtype, d, V));
+  return std::max(st, 0.38 * st + rows * 2.0 * V * d / 1440e6);
+}
+
 bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all) {
-  // One pass over everything against the least that walking can cost: the
-  // final layer of every position, and then empty passes (band), or one more
-  // layer of every position (walk_all, where every position walks).
-  const double st = stream_us(dtype, d, V), row = row_us(dtype, d, V);
-  const double one = std::max(st, row * (double)K * (double)cap);
-  const double first = std::max(st, row * (double)cap);
-  const int pr = lazy_pass_rows(dtype, d, V);
-  int passes = 0;
-  for (int rem = K - 1, g = 1; rem > 0; g *= 2, ++passes) rem -= lazy_group((int)std::max(cap, 1LL), rem, g, pr);
-  return one <= first + (walk_all && K > 1 ? first : 0.0) + kPassUs * passes;
+  // One pass over everything against walking. In the band few positions walk:
+  // one pass if it costs no more than the least that walking can, the final
+  // layer of every position and then empty passes. Where every position walks
+  // (walk_all) the least is one more layer of each, the most every layer of
+  // each: one pass if it costs no more than the middle of the two. It then
+  // loses less against walking that ends at once than it gains against walking
+  // that does not (200 positions, K = 4: one pass 655 us; walking 510 to 990).
+  if (K == 1) return true;
+  const double one = pass_us(dtype, (double)K * (double)cap, d, V);
+  const int n = (int)std::max(cap, 1LL), pr = lazy_pass_rows(dtype, d, V);
+  double least = pass_us(dtype, n, d, V), most = least;
+  if (walk_all) least += least;
+  for (int rem = K - 1, g = 1; rem > 0; g *= 2) {
+    const int take = lazy_group(n, rem, g, pr);
+    most += kPassUs + pass_us(dtype, (double)n * take, d, V);
+    least += kPassUs;
+    rem -= take;
+  }
+  return one <= (walk_all ? 0.5 * (least + most) : least);
 }
 
 hipError_t launch_projection(const Launch& a, hipStream_t s) {

@@ -288,28 +288,60 @@ def test_lazy_projection_walking_every_position(name, ov, seed):
         assert np.abs(g["drop"][same] - eager["drop"][same]).max(initial=0.0) <= 2 * CONF_TOL
 
 
-# Lazy calls that walk in several passes (smaller ones are projected in one): matrices large enough that a pass is
-# worth fewer rows than the call has. bf16 passes of 1, then several layers a position; the rows of the later passes
-# fall in different size classes with the share of positions in the band; above 256 positions counts are read back.
-LAZY_PASS_CASES = [
-    ("band_few", dict(B=1, L=256, K=8, d=1024, V=20011, n_masked=250, sharp=("calibrated", -3.0, 1.0)), False, 71),
-    ("band_some", dict(B=1, L=256, K=8, d=1024, V=20011, n_masked=250, sharp=("calibrated", -1.0, 2.0)), False, 72),
-    ("every_position", dict(B=1, L=256, K=8, d=1024, V=20011, n_masked=250), False, 73),
-    ("read_back", dict(B=2, L=200, K=6, d=1024, V=20011, n_masked=190, sharp=("calibrated", -1.0, 2.0)), False, 74),
-    ("norm", dict(B=1, L=200, K=8, d=1000, V=20011, n_masked=190, sharp=("calibrated", -1.0, 2.0)), True, 75),
-    ("f32", dict(B=1, L=128, K=6, d=512, V=8009, n_masked=120, dtype="f32", sharp=("calibrated", -1.0, 2.0)), False, 76),
-    ("f32_norm_every_position", dict(B=2, L=80, K=6, d=514, V=8009, n_masked=70, dtype="f32"), True, 77),
-]
+def test_lazy_pass_over_several_layers():
+    # a pass after the first that takes all the layers left of about 60 positions
+    w = make_workload(CONFIGS["llada_late"].with_(name="lazypass", B=1, L=256, K=8, d=1024, V=20011, n_masked=250,
+                                                  masked_frac=None, sharp=("calibrated", -1.0, 1.0), unstable_frac=0.25,
+                                                  layer_jitter=0.3), 71)
+    _check(w, dataclasses.replace(O.LLADA, lazy=True))
 
 
-@pytest.mark.parametrize("name,ov,norm,seed", LAZY_PASS_CASES, ids=[c[0] for c in LAZY_PASS_CASES])
-def test_lazy_passes(name, ov, norm, seed):
-    base = CONFIGS["llada_late"].with_(**{**dict(name="lazypass_" + name, masked_frac=None, sharp=("calibrated",),
-                                                 unstable_frac=0.25, layer_jitter=0.3), **ov})
-    w = make_workload(base, seed)
-    every = "every" in name
-    _check(w, dataclasses.replace(O.LLADA, lazy=True, lazy_all=every),
-           norm=(_gain(w, seed), 1e-5, False) if norm else None)
+# Calls that walk in several passes need matrices on which a pass is worth fewer rows than the call has, so these are
+# drawn on the GPU and compared with the eager projection: passes of 1, 2, 4 .. layers with the counts on the device
+# (up to 256 positions) or read back, in every size class.
+@pytest.mark.parametrize("B,n,K,dtype,every,norm", [
+    (1, 250, 8, "bf16", False, False), (1, 250, 8, "bf16", True, False), (1, 256, 4, "bf16", True, True),
+    (2, 190, 6, "bf16", False, True), (2, 190, 6, "bf16", True, False), (1, 40, 8, "bf16", True, False),
+    (1, 110, 6, "f32", True, False), (3, 100, 5, "f32", False, True)])
+def test_lazy_passes_against_the_eager_projection(B, n, K, dtype, every, norm):
+    V, d, L, dev = 64007, 3080, 300, "cuda:0"
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(B * n + K)
+    rand = lambda *s: torch.rand(s, generator=g, device=dev)
+    w_u = (torch.randn((V, d), generator=g, device=dev) / math.sqrt(d)).to(dt)
+    mask = torch.zeros((B, L), dtype=torch.uint8, device=dev)
+    for b in range(B):
+        mask[b, rand(L).argsort()[:n]] = 1
+    target = torch.randint(0, V, (B, L), generator=g, device=dev)
+    level = math.log(V) + 4.0 * rand(B, L)            # most positions between theta_c and theta_h
+    depth = torch.randint(0, K + 1, (B, L), generator=g, device=dev)   # layers below hold another token
+    hidden = torch.empty((K, B, L, d), dtype=dt, device=dev)
+    for l in range(K):
+        t = torch.where(K - 1 - l >= depth, (target + 1) % V, target) if l < K - 1 else target
+        w = w_u[t].float()
+        x = w * ((level + 0.3 * torch.randn((B, L), generator=g, device=dev)) / w.square().sum(-1)).unsqueeze(-1)
+        hidden[l] = x + torch.randn((B, L, d), generator=g, device=dev)
+    kw = dict(norm_weight=(0.75 + 0.5 * rand(d)).to(dt), norm_eps=1e-5) if norm else {}
+    P = O.LLADA
+    res = [{k: v.cpu().numpy() for k, v in rpd.score_commit(hidden, w_u, mask, gpu_params(p), max_masked=B * n,
+                                                            layer_stats=True, **kw).items()}
+           for p in (P, dataclasses.replace(P, lazy=True, lazy_all=every))]
+    e, z = res
+    m = mask.cpu().numpy() != 0
+    for k in ("token", "commit", "flags", "n_commit"):
+        np.testing.assert_array_equal(e[k], z[k], err_msg=k)
+    walks = m & (every | ((z["confidence"] >= P.theta_c) & (z["confidence"] < P.theta_h)))
+    assert walks.sum() > 0.2 * m.sum()
+    np.testing.assert_array_equal(z["persistence"][walks], e["persistence"][walks])
+    assert np.abs(z["drop"][walks] - e["drop"][walks]).max() <= 2 * CONF_TOL
+    assert (z["persistence"][m & ~walks] == -1).all() and np.isnan(z["drop"][m & ~walks]).all()
+    seen = np.where(walks, np.minimum(e["persistence"] + 1, K), 1)
+    for l in range(K):
+        s = m & (l >= K - seen)
+        np.testing.assert_array_equal(z["layer_argmax"][l][s], e["layer_argmax"][l][s])
+        assert np.abs(z["layer_conf"][l][s] - e["layer_conf"][l][s]).max(initial=0.0) <= CONF_TOL
+        assert np.abs(z["layer_entropy"][l][s] - e["layer_entropy"][l][s]).max(initial=0.0) <= ENTROPY_TOL
+        assert (z["layer_argmax"][l][m & ~s] == -1).all() and np.isnan(z["layer_conf"][l][m & ~s]).all()
 
 
 @pytest.mark.parametrize("n", [3, 12])
