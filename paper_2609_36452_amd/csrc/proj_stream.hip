@@ -99,10 +99,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
   // Otherwise the W_U loads of the first two chunks go out before anything
   // waits (the mask bytes ahead of them, so that the scan does not wait for
   // HBM, measured 0.4% slower at 32 rows).
-  int R = 0, G = 1;   // G: layers taken of each listed position
+  int R = 0, per = K;   // per: rows (layers) of a position
   if (!FC && rowoff) {
     R = *n_ptr;
-    G = *grp;
+    per = *grp;
     if (rt * TR >= R) return;
   }
   if (has_job && nchf > 0) {
@@ -135,19 +135,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
     xrow[u] = row;
     xpiece[u] = (q & 7) ^ ((row >> 1) & 7);
     const int r = r0 + row < R ? r0 + row : r0;
-    if (xrows) {   // normalized rows, already in projected-row (or list) order
+    if (!FC && xrows) {   // normalized rows, already in projected-row (or list) order
       xa[u] = (long long)r * d + xpiece[u] * 8;
-    } else if (rowoff) {   // an explicit row list
-      const int j = r / G;
-      xa[u] = rowoff[j] - (r - j * G) * ((long long)B * L * d) + xpiece[u] * 8;
     } else {
-      const int p = r / K, l = r - p * K;
-      const int pos = FC ? s_pos[p] : rows[p];
-      const int b = pos / L, i = pos - b * L;
-      xa[u] = (((long long)l * B + b) * L + i) * (long long)d + xpiece[u] * 8;
+      const int p = r / per, l = r - p * per;
+      if (!FC && rowoff)   // an explicit row list, its layers from the first one down
+        xa[u] = rowoff[p] - l * ((long long)B * L * d) + xpiece[u] * 8;
+      else
+        xa[u] = ((long long)l * B * L + (FC ? s_pos[p] : rows[p])) * (long long)d + xpiece[u] * 8;
     }
   }
-  const uint16_t* __restrict__ xsrc = xrows ? xrows : hidden;
+  const uint16_t* __restrict__ xsrc = !FC && xrows ? xrows : hidden;
   const int xpc = (tid & 7) * 8;       // LDS piece of this thread's hidden-row loads
   // fragments: row base + (lane & 31), logical piece 2s + (lane >> 5)
   const int fr = lane & 31, fsw = (fr >> 1) & 7, fhi = lane >> 5;
