@@ -158,16 +158,26 @@ class CountSlot {
  public:
   CountSlot(bool allowed, hipStream_t s) {
     if (!allowed) return;
+    // A call that fails here only means that the count is copied: its error is
+    // taken back from the runtime, which would otherwise hand it to the check
+    // of the next launch.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (cap != hipStreamCaptureStatusNone) return;
     std::call_once(g_slots_once, [] {
       // allowed also while another thread captures a graph
       hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-      if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
-      void* p = nullptr;
-      if (hipHostMalloc(&p, sizeof(Slot) * kSlots, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess)
-        g_slots = static_cast<Slot*>(p);
-      (void)hipThreadExchangeStreamCaptureMode(&mode);
+      hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+      if (e == hipSuccess) {
+        void* p = nullptr;
+        e = hipHostMalloc(&p, sizeof(Slot) * kSlots, hipHostMallocPortable | hipHostMallocCoherent);
+        if (e == hipSuccess) g_slots = static_cast<Slot*>(p);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+      }
+      if (e != hipSuccess) (void)hipGetLastError();
     });
     if (!g_slots) return;
     uint64_t f = g_slots_free.load(std::memory_order_relaxed);
