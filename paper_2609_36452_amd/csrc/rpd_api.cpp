@@ -186,7 +186,9 @@ class CountSlot {
     if (f) index_ = __builtin_ctzll(f);
   }
   ~CountSlot() {
-    if (index_ >= 0) g_slots_free.fetch_or(1ull << index_, std::memory_order_release);
+    // A slot that was armed and not waited for (the call failed in between) is
+    // not given back: a kernel may yet store to it, when another call waits there.
+    if (index_ >= 0 && !armed_) g_slots_free.fetch_or(1ull << index_, std::memory_order_release);
   }
   CountSlot(const CountSlot&) = delete;
   CountSlot& operator=(const CountSlot&) = delete;
@@ -194,6 +196,7 @@ class CountSlot {
   // where the next kernel is to store the count; NULL: it is copied from the device
   int32_t* arm() {
     if (index_ < 0) return nullptr;
+    armed_ = true;
     __atomic_store_n(&g_slots[index_].count, -1, __ATOMIC_RELEASE);
     return &g_slots[index_].count;
   }
@@ -202,17 +205,14 @@ class CountSlot {
     if (index_ >= 0) {
       const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
       for (int k = 1;; ++k) {
-        *out = __atomic_load_n(&g_slots[index_].count, __ATOMIC_ACQUIRE);
-        if (*out >= 0) return hipSuccess;
+        if (arrived(out)) return hipSuccess;
         __builtin_ia32_pause();
         if (k % 64 == 0 && std::chrono::steady_clock::now() > end) break;
       }
       // much work before it on the stream (or a kernel that will not run): wait without polling
       const hipError_t e = hipStreamSynchronize(s);
-      if (e == hipSuccess) *out = __atomic_load_n(&g_slots[index_].count, __ATOMIC_ACQUIRE);
-      if (e == hipSuccess && *out >= 0) return hipSuccess;
-      index_ = -1;   // not given back: a kernel may yet store to it
-      return e == hipSuccess ? hipErrorUnknown : e;
+      if (e != hipSuccess) return e;
+      return arrived(out) ? hipSuccess : hipErrorUnknown;
     }
     hipError_t e = hipMemcpyAsync(out, dev, sizeof *out, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -220,7 +220,13 @@ class CountSlot {
   }
 
  private:
+  bool arrived(int32_t* out) {
+    *out = __atomic_load_n(&g_slots[index_].count, __ATOMIC_ACQUIRE);
+    armed_ = *out < 0;
+    return !armed_;
+  }
   int index_ = -1;
+  bool armed_ = false;   // a kernel may yet store to the slot
 };
 
 // Lazy layerwise projection: projection passes from the final layer down over

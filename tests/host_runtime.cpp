@@ -2,8 +2,8 @@
 // library's host code (rpd_api.cpp, proj_plan.cpp) without a GPU. Launches
 // are recorded instead of run. Of the kernels, only the two that count
 // positions leave something behind: the count, in device memory and, where the
-// launch asks for it, in host memory, when the stream is waited for (the work
-// on a stream completes no earlier here).
+// launch asks for it, in host memory, when the stream is waited for or another
+// counting kernel is enqueued behind it (no earlier here).
 //
 // As in the runtime, an error stays the thread's last error until
 // hipGetLastError takes it, a call that succeeds does not clear it, and a
@@ -44,6 +44,7 @@ void complete() {
 }
 
 hipError_t count_kernel(int32_t* dev, int32_t* host) {
+  complete();
   const int n = g_counts.empty() ? 0 : g_counts.front();
   if (!g_counts.empty()) g_counts.pop_front();
   g_pending.push_back({dev, n});
@@ -65,7 +66,6 @@ void host_reset() {
 }
 void host_set_last_error(int e) { g_last = static_cast<hipError_t>(e); }
 void host_add_count(int n) { g_counts.push_back(n); }
-void host_complete() { complete(); }
 const char* host_log() { return g_log.c_str(); }
 }
 

@@ -65,3 +65,13 @@ def test_without_a_pinned_slot_the_count_is_copied(host, what):
         assert s == 0, host.rpd_last_error()
         assert log[:3] == ["compact", "copy", "sync"] and log[3:] == ["big24" if n == 24 else "stream7",
                                                                       f"reduce{n}", "commit0"]
+
+
+def test_a_slot_that_a_kernel_may_still_store_to_is_not_given_back(host):
+    # the launch check reports an earlier failure of the program's own although the compaction is enqueued: the call
+    # fails, and the compaction stores its count later, when the next call already waits for another
+    host.host_set_last_error(INVALID_VALUE)
+    host.host_add_count(64)
+    assert _call(host)[0] == 6
+    host.host_add_count(7)
+    assert _call(host) == (0, ["compact", "sync", "stream7", "reduce7", "commit0"])
