@@ -10,17 +10,24 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
   ProjPlan p{};
   if (rows_cap < 1) rows_cap = 1;
   if (dtype == 1) {   // fp32
-    // the tile height (32..128 rows) that pads the rows least, the tallest of
-    // equals (it reads W_U least); a launch that would leave most of the 256
-    // CUs idle takes 64 x 32 tiles instead
+    // The tile height (32..128 rows) whose padded rows cost least, a row of a
+    // shorter tile costing more (it reads W_U more often: 1024 rows at d = 4096,
+    // V = 126464 in tiles of 128, 96, 64 and 32 rows 8.15, 8.38 per padded row,
+    // 8.17 and 8.79 ms; 4096 rows at d = 1024, V = 32000 2.17, 2.21, 2.21 and
+    // 2.33); the tallest of equals. A launch that would leave most of the 256
+    // CUs idle takes 64 x 32 tiles instead.
+    static constexpr struct {
+      int rows;
+      double cost;   // of a row, against the tallest tile's
+    } kHeights[] = {{128, 1.0}, {96, 1.02}, {64, 1.02}, {32, 1.07}};
     p.variant = PROJ_F32;
     p.vocab_cap = kF32TileVocab;
-    long long best = 0;
-    for (int tr = 128; tr >= 32; tr -= 32) {
-      const long long pad = (rows_cap + tr - 1) / tr * tr;
-      if (best == 0 || pad < best) {
-        best = pad;
-        p.rows_per_tile = tr;
+    double best = 0.0;
+    for (const auto& h : kHeights) {
+      const double cost = (double)((rows_cap + h.rows - 1) / h.rows * h.rows) * h.cost;
+      if (best == 0.0 || cost < best) {
+        best = cost;
+        p.rows_per_tile = h.rows;
       }
     }
     p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
@@ -56,7 +63,11 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
     p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
   }
   p.nrt = (int)((rows_cap + p.rows_per_tile - 1) / p.rows_per_tile);
-  p.split_rows = p.nrt >= 8 ? 1 : 0;
+  // fp32: the XCDs own whole row tiles only where each gets as many, else
+  // ranges of the vocabulary (nine row tiles at d = 4096, V = 126464: 864 rows
+  // 13.2 -> 7.0 ms, 1136 rows 17.2 -> 9.2; 32 of them at d = 1024, V = 32000:
+  // 2.15 ms against 2.16)
+  p.split_rows = p.nrt >= 8 && (dtype != 1 || p.nrt % 8 == 0) ? 1 : 0;
   p.per_xcd = p.split_rows ? ((p.nrt + 7) / 8) * p.nvt : ((p.nvt + 7) / 8) * p.nrt;
   p.grid = 8 * p.per_xcd;
   return p;

@@ -1,5 +1,5 @@
 """The library's host code on a stand-in HIP runtime (host_runtime.cpp): what
-a call does when a runtime call fails, and which launches it makes."""
+a call does when a runtime call fails, and what it plans and launches."""
 import ctypes
 import os
 import shutil
@@ -75,3 +75,34 @@ def test_a_slot_that_a_kernel_may_still_store_to_is_not_given_back(host):
     assert _call(host)[0] == 6
     host.host_add_count(7)
     assert _call(host) == (0, ["compact", "sync", "stream7", "reduce7", "commit0"])
+
+
+class _Plan(ctypes.Structure):   # rpd::ProjPlan
+    _fields_ = [(n, ctypes.c_int) for n in ("variant", "rows_per_tile", "vocab_cap", "nvt", "nrt", "per_xcd",
+                                            "split_rows", "grid")]
+
+
+def _plan(L, dtype, rows, V):
+    f = L._ZN3rpd15plan_projectionEixi   # rpd::plan_projection(int, long long, int)
+    f.restype, f.argtypes = _Plan, [ctypes.c_int, ctypes.c_longlong, ctypes.c_int]
+    return f(dtype, rows, V)
+
+
+def _busiest(p):
+    """Tiles of the XCD that has most of them."""
+    share = lambda n: max((x + 1) * n // 8 - x * n // 8 for x in range(8))   # noqa: E731
+    return share(p.nrt) * p.nvt if p.split_rows else share(p.nvt) * p.nrt
+
+
+@pytest.mark.parametrize("V", [126464, 32000])
+def test_fp32_tiles_are_spread_evenly_over_the_xcds(host, V):
+    for rows in [*range(1, 1400, 7), 2048, 2049, 4096, 4400, 12288]:
+        p = _plan(host, 1, rows, V)
+        assert 8 * _busiest(p) <= 1.03 * p.nvt * p.nrt, (rows, p.rows_per_tile, p.nrt)
+
+
+def test_fp32_tile_height_by_the_cost_of_its_rows(host):
+    # 128-row tiles cost least a row, then 96 and 64, then 32: a shorter tile has to save its padding
+    rows = (32, 48, 96, 128, 160, 208, 224, 240, 256, 288, 320, 352, 384, 544, 640, 736, 800, 864, 992, 1136)
+    assert [_plan(host, 1, r, 126464).rows_per_tile for r in rows] == \
+        [32, 64, 96, 128, 32, 32, 32, 128, 128, 96, 64, 32, 128, 32, 128, 128, 64, 96, 128, 128]
