@@ -73,49 +73,71 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
   return p;
 }
 
-// Time of one projection pass, for the lazy rules below: streaming W_U at the
-// rate the smallest row counts reach (6.7 TB/s in bf16, 5.6 in fp32), or the
-// rows' matrix time at the rate of 256 rows (1.05 PFLOP/s in bf16; 128 TFLOP/s
-// in fp32), whichever is more. kPassUs: what a pass costs besides, its
-// launches (up to four projections of which one runs, reduction, listing:
-// about 5 us each on the stream).
-static constexpr double kPassUs = 30.0;
-static double stream_us(int dtype, int d, int V) { return (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / 6.7e6); }
+// ---------------------------------------------------------- lazy passes --
+//
+// How many layers a lazy pass takes, and whether a call walks at all, is decided
+// before anything is known about the walk: positions may stop at the first layer
+// below the final one or agree on down to the last. The two rules below bound
+// what a call loses against one pass per layer where all stop at once.
+
+// Streaming W_U (6.9 TB/s in bf16, 5.6 in fp32), and one row's matrix time (at 256
+// rows 1.05 PFLOP/s in bf16, 128 TFLOP/s in fp32).
+static double stream_us(int dtype, int d, int V) { return (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / 6.9e6); }
 static double row_us(int dtype, int d, int V) { return 2.0 * V * d / (dtype == 1 ? 128e6 : 1050e6); }
 
+// What a pass costs beside the projection that runs (its listing, reduction and
+// up to three projections that exit at once), and what a pass does that finds no
+// position (100 and 256 positions at d = 4096, V = 126464 that all stop at the
+// first layer: 377 and 517 us with K = 2, 400 and 530 with K = 4, 436 and 551 with
+// K = 8; the projections of the first two passes take 2 * 171 and 2 * 240).
+static constexpr double kPassUs = 17.0, kEmptyPassUs = 11.0;
+
+// Rows up to which layers taken along in vain cost at most half of a pass over
+// few rows, which is what each saves where its positions walk on. At d = 4096,
+// V = 126464 (246 rows), K = 4, half of the positions in the band, one layer a
+// pass -> so: all stopping at once 125 positions 375 -> 445 us, 200 455 -> 510;
+// all agreeing 125 positions 695 -> 460, 200 800 -> 680. Passes of up to twice as
+// many rows lose as much as they gain (200 and 256 positions 600 and 630 us
+// whether they stop or walk; one layer a pass 455 and 455 to 800 and 800).
 int lazy_pass_rows(int dtype, int d, int V) {
-  const double r = (stream_us(dtype, d, V) + kPassUs) / row_us(dtype, d, V);
-  return r < 1.0 ? 1 : (r > 1e6 ? 1000000 : (int)r);
+  const double r = (1.5 * stream_us(dtype, d, V) + kPassUs) / row_us(dtype, d, V);
+  const int n = (int)std::min(std::max(r, 1.0), dtype == 1 ? 128.0 : (double)kBigTileRows);   // one row tile
+  // whole fp32 tiles: there the matrix time of the rows that pad the last one counts
+  return dtype == 1 && n > 32 ? n / 32 * 32 : n;
 }
 
-// A pass over `rows` rows: in bf16 above the ridge an affine fit (at d = 4096,
-// V = 126464: 244 us at 256 rows, 440 at 512, 600 at 768, 815 at 1024).
-static double pass_us(int dtype, double rows, int d, int V) {
+// A pass over `rows` rows, in tiles of which the busiest XCD has its share. In
+// bf16 a fit: the MFMA tiles read W_U 12% slower than the streaming kernel, and
+// padding rows cost two thirds of a row (d = 4096, V = 126464, the projection alone:
+// 64 rows 153 us, 128 171, 192 193, 256 240, 384 352, 400 418, 512 436, 576 506, 768
+// 634, 1024 822; the fit 156, 174, 191, 240, 339, 410, 437, 486, 634, 831. d = 2048,
+// V = 32000: 64 rows 26, 256 39, 512 53, 1024 111; the fit 25, 36, 60, 110).
+static double pass_us(int dtype, long long rows, int d, int V) {
+  const ProjPlan p = plan_projection(dtype, rows, V);
   const double st = stream_us(dtype, d, V);
-  if (dtype == 1) return std::max(st, rows * row_us(dtype, d, V));
-  return std::max(st, 0.38 * st + rows * 2.0 * V * d / 1440e6);
+  const double padded = (double)(p.split_rows ? (p.nrt + 7) / 8 * 8 : p.nrt) * p.rows_per_tile;
+  if (dtype == 1) return 6.0 + std::max(st, padded * row_us(dtype, d, V));
+  const double matrix = 0.25 * st + (0.68 * padded + 0.32 * (double)rows) * 2.0 * V * d / 1345e6;
+  return 6.0 + std::max(rows <= kStreamMaxRows ? st : 1.12 * st, matrix);
 }
 
+// Whether one pass over every layer of every position takes the place of
+// walking. Where every position walks (walk_all): if it costs at most a fifth
+// more than the least that walking with one layer a pass can, the final layer, one more
+// pass and passes that find no position. (d = 4096, V = 126464, K = 4: 100
+// positions 425 us against 395 where they stop at once and 740 where all agree, 125
+// positions 445 against 385 and 725. At 150 and 200 one pass takes 615 and 790,
+// walking 431 and 510 to 830 and 1000.) In the band: if it costs no more than the
+// final layer, 30 us for the next pass, which takes more as soon as a single
+// position is in the band, and passes that find none.
 bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all) {
-  // One pass over everything against walking. In the band few positions walk:
-  // one pass if it costs no more than the least that walking can, the final
-  // layer of every position and then empty passes. Where every position walks
-  // (walk_all) the least is one more layer of each, the most every layer of
-  // each: one pass if it costs no more than the middle of the two. It then
-  // loses less against walking that ends at once than it gains against walking
-  // that does not (200 positions, K = 4: one pass 655 us; walking 510 to 990).
   if (K == 1) return true;
-  const double one = pass_us(dtype, (double)K * (double)cap, d, V);
   const int n = (int)std::max(cap, 1LL), pr = lazy_pass_rows(dtype, d, V);
-  double least = pass_us(dtype, n, d, V), most = least;
-  if (walk_all) least += least;
-  for (int rem = K - 1, g = 1; rem > 0; g *= 2) {
-    const int take = lazy_group(n, rem, g, pr);
-    most += kPassUs + pass_us(dtype, (double)n * take, d, V);
-    least += kPassUs;
-    rem -= take;
-  }
-  return one <= (walk_all ? 0.5 * (least + most) : least);
+  const double one = pass_us(dtype, (long long)K * n, d, V), final_layer = pass_us(dtype, n, d, V);
+  if (walk_all) return one <= 1.2 * (2 * final_layer + kPassUs + (K - 2) * kEmptyPassUs);
+  int passes = 0;
+  for (int rem = K - 1; rem > 0;) rem -= lazy_group(n, rem, lazy_min_group(++passes), pr);
+  return one <= final_layer + 30.0 + (passes - 1) * kEmptyPassUs;
 }
 
 hipError_t launch_projection(const Launch& a, hipStream_t s) {

@@ -245,12 +245,12 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, M
     // While the bound on the positions is at most kLazyGateRows the host reads
     // nothing back: the pass is launched once per size class the row count may
     // fall in, each taking its count from the device as that class's count, 0
-    // unless it is the class, so all but one exit at once; and each pass takes
-    // at least twice the layers of the one before, so that few are enqueued.
-    // Above the bound the count is read back (one stream synchronisation) and
-    // the pass planned for it. A single pass planned for the bound would run
-    // an MFMA tile whatever the count (lazy call at 256 positions: 838 -> 1010
-    // us), and above 256 rows its few row tiles would land on a few XCDs.
+    // unless it is the class, so all but one exit at once. Above the bound the
+    // host waits for the count (CountSlot) and plans the pass for it. A single
+    // pass planned for the bound would run an MFMA tile whatever the count (lazy
+    // call at 256 positions: 838 -> 1010 us), and above 256 rows its few row
+    // tiles would land on a few XCDs.
+
     // a pass of at most `cap` rows whose count is at `count`
     auto pass_launch = [&](int32_t* count, long long cap) {
       rpd::Launch ap = a;
@@ -262,12 +262,13 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, M
       return ap;
     };
     // pass 0, listed by the compaction: the final layer of every masked position
-    int rem = a.K, group = 1, min_group = 1;
+    int rem = a.K, group = 1;
     bool known = true;
     for (int t = 0;; ++t) {
       long long rows_cap = m_host;
       if (t > 0) {
         known = m_host > rpd::kLazyGateRows;
+        const int min_group = known ? 1 : rpd::lazy_min_group(t);
         if ((e = rpd::launch_lazy_next(a, dtype, min_group, pass_rows, known ? slot.arm() : nullptr, s)) != hipSuccess)
           return e;
         if (known) {
@@ -279,8 +280,7 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, M
         // with the count known, the layers the device takes; else the fewest it may (it takes more of fewer positions)
         group = rpd::lazy_group(m_host, rem, min_group, pass_rows);
         rows_cap = known ? (long long)m_host * group
-                         : std::min((long long)m_host * rem,
-                                    std::max(2ll * pass_rows, (long long)m_host * min_group));
+                         : std::min((long long)m_host * rem, std::max((long long)pass_rows, (long long)m_host * min_group));
       }
       // the pass's rows are normalized once and reduced once; in between one
       // projection, or one per size class, of which only the count's class
@@ -303,7 +303,6 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, M
       }
       rem -= group;
       if (rem <= 0) break;
-      min_group = t == 0 || m_host > rpd::kLazyGateRows ? 1 : 2 * min_group;
     }
   }
   if ((e = mark(2)) != hipSuccess) return e;

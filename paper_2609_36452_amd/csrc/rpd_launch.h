@@ -45,7 +45,7 @@ struct LazyClasses {
   int cap[kLazyClasses - 1];
 };
 inline LazyClasses lazy_classes(int dtype) {
-  return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 256}};
+  return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 192}};
 }
 // largest canvas (B * L) whose compaction the projection does itself with a single row tile
 constexpr int kFusedCompactMax = 2048;
@@ -73,16 +73,19 @@ int lazy_pass_rows(int dtype, int d, int V);
 // every position in one pass
 bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all);
 // Layers that the next lazy pass takes of each of its m positions, `rem`
-// layers being left: all of them while that is no more than twice the rows a
-// pass is worth, else as many as a pass is worth, at least min_group. Never
+// layers being left: as many as a pass is worth, at least min_group. Never
 // fewer for fewer positions.
 __host__ __device__ inline int lazy_group(int m, int rem, int min_group, int pass_rows) {
   if (m <= 0 || rem <= 0) return 0;
-  if ((long long)m * rem <= 2ll * pass_rows) return rem;
   int g = pass_rows / m;
   g = g < min_group ? min_group : g;
   return g < rem ? g : rem;
 }
+
+// The fewest layers that pass t (from 1) takes of each position whose count only
+// the device knows: twice as many from the third pass on, so that few passes
+// are enqueued where K is large.
+inline int lazy_min_group(int t) { return t < 3 ? 1 : 1 << (t - 2); }
 
 // per-position state of the lazy layerwise projection (lazy.hip)
 struct LazyState {

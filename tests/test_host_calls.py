@@ -2,6 +2,7 @@
 a call does when a runtime call fails, and what it plans and launches."""
 import ctypes
 import os
+import re
 import shutil
 import subprocess
 
@@ -43,6 +44,7 @@ def _call(L, max_masked=-1, K=4, B=1, n=64, d=4096, V=126464, dtype=0, flags=0):
     o = rpd.RpdOutputs(*([4096] * 10 + [None] * 4))
     need = L.rpd_workspace_size(ctypes.byref(p))
     buf = ctypes.create_string_buffer(512)     # the header is all that the stand-in kernels write
+    L.kept = getattr(L, "kept", []) + [buf]    # which they may do after the call
     at = (ctypes.addressof(buf) + 255) // 256 * 256
     before = len(L.host_log())
     s = L.rpd_score_commit(ctypes.byref(p), ctypes.byref(q), ctypes.byref(o), ctypes.c_void_p(at),
@@ -106,3 +108,57 @@ def test_fp32_tile_height_by_the_cost_of_its_rows(host):
     rows = (32, 48, 96, 128, 160, 208, 224, 240, 256, 288, 320, 352, 384, 544, 640, 736, 800, 864, 992, 1136)
     assert [_plan(host, 1, r, 126464).rows_per_tile for r in rows] == \
         [32, 64, 96, 128, 32, 32, 32, 128, 128, 96, 64, 32, 128, 32, 128, 128, 64, 96, 128, 128]
+
+
+LAZY, LAZY_ALL = 1, 3
+
+
+def _projections(log):
+    """Launches of a lazy call, pass by pass: bounds on the rows of the projections in it."""
+    passes = [[]]
+    for w in log:
+        if w == "next":
+            passes.append([])
+        elif w.startswith(("big", "stream", "f32_")):
+            passes[-1].append(int(re.search(r"\d+$", w.replace("f32_", "")).group()))
+    return passes
+
+
+def test_lazy_calls_that_project_every_layer_at_once(host):
+    # Where every position walks, one pass over all layers may cost a fifth more than the least that walking can (d =
+    # 4096, V = 126464: 128 positions at K = 4 are 512 rows, two 256-row tiles; 72 at K = 8 three 192-row tiles)
+    one = lambda n, K, flags: "score%d" % n not in _call(host, n, K=K, n=256, flags=flags)[1]   # noqa: E731
+    assert [n for n in range(1, 257) if one(n, 4, LAZY_ALL)] == list(range(1, 129))
+    assert [n for n in range(1, 257) if one(n, 8, LAZY_ALL)] == list(range(1, 73))
+    assert all(one(n, 2, LAZY_ALL) for n in range(1, 257)) and all(one(n, 1, LAZY) for n in range(1, 257))
+    # in the band, where one more pass over few positions is all that walking is likely to take, far fewer
+    assert not one(64, 4, LAZY) and one(24, 4, LAZY)
+
+
+@pytest.mark.parametrize("K", [3, 4, 8, 20])
+@pytest.mark.parametrize("flags", [LAZY, LAZY_ALL])
+def test_lazy_passes_take_no_more_rows_than_are_worth_one(host, K, flags):
+    # the first two passes after the final layer: the rows of one tile, or a layer of every position; later ones at
+    # least 2, 4 .. layers, and the layers add up
+    for n in (70, 129, 160, 200, 256):
+        s, log = _call(host, n, K=K, n=256, flags=flags)
+        if "score%d" % n not in log:
+            continue
+        passes = _projections(log)
+        assert s == 0 and passes[0] == [n]
+        for t, rows in enumerate(passes[1:], 1):
+            assert max(rows) <= max(256, n * max(1, 2 ** (t - 2))), (n, t, rows)
+            assert sorted(rows) == rows and len(rows) <= 4
+        assert 2 ** (len(passes) - 4) < K
+
+
+def test_lazy_counts_above_the_bound_are_waited_for(host):
+    # 300 positions, of which 280, 150 and then none walk on: two counts through the slot, then size classes
+    for c in (300, 280, 150):   # the first by the compaction
+        host.host_add_count(c)
+    s, log = _call(host, 300, K=6, n=512, flags=LAZY_ALL)
+    assert s == 0 and log[:3] == ["compact", "big300", "walk300"]
+    assert log[3:7] == ["next", "sync", "big280", "walk280"] and log[7:11] == ["next", "sync", "big150", "walk150"]
+    assert "sync" not in log[11:] and log[-2:] == ["score300", "commit0"]
+    passes = _projections(log)[3:]
+    assert passes and all(len(p) > 1 for p in passes)
