@@ -115,9 +115,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && NB >= 2) ? 2 : 1) void k_proj_
   }
   if (FC) {
     // one row tile (r0 = 0): rows 0 .. TR-1 need positions 0 .. TR-1 at most
-    MaskBytes<NW> mb;
-    mb.load(ca);
-    R = compact_in_workgroup<NW>(ca, mb, s_pos, 0, TR, s_wave) * K;
+    R = compact_in_workgroup<NW>(ca, MaskInTurn{}, s_pos, 0, TR, s_wave) * K;
     if (!has_job) return;
   } else if (!rowoff) {
     R = *n_ptr * K;   // an explicit row list (above) counts rows, not positions

@@ -160,6 +160,17 @@ struct MaskBytes {
       v[u] = i < ca.BL ? ca.mask[i] : 0;
     }
   }
+  static constexpr int kUnroll = N;
+  __device__ __forceinline__ bool at(const CompactArgs&, int u, int) const { return v[u] != 0; }
+};
+
+// or loaded as the scan comes to them, one round of the workgroup's threads
+// after another, where the loads before them have to return first in any case
+// (the streaming projection): what loading all of them first costs a canvas of
+// one round, up to 0.4 us, is not won back there
+struct MaskInTurn {
+  static constexpr int kUnroll = 1;
+  __device__ __forceinline__ bool at(const CompactArgs& ca, int, int i) const { return i < ca.BL && ca.mask[i] != 0; }
 };
 
 // a barrier that publishes LDS stores and waits for no global load
@@ -170,17 +181,17 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <int NW>
-__device__ __forceinline__ int compact_in_workgroup(const CompactArgs& ca, const MaskBytes<NW>& mb, int* s_pos,
-                                                    int p0, int need, int* s_wave) {
+template <int NW, class Mask>
+__device__ __forceinline__ int compact_in_workgroup(const CompactArgs& ca, const Mask& mask, int* s_pos, int p0,
+                                                    int need, int* s_wave) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const bool publish = blockIdx.x == 0;
   int carry = 0;
-#pragma unroll
-  for (int u = 0; u < MaskBytes<NW>::N; ++u) {
+#pragma unroll(Mask::kUnroll)
+  for (int u = 0; u < kFusedCompactMax / (NW * 64); ++u) {
     const int base = u * NW * 64, i = base + threadIdx.x;
     if (base >= ca.BL) break;
-    const bool f = mb.v[u] != 0;
+    const bool f = mask.at(ca, u, i);
     const unsigned long long bal = __ballot(f);
     const int before = __popcll(bal & ((1ull << lane) - 1ull));
     if (lane == 0) s_wave[wid] = __popcll(bal);
