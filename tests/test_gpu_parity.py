@@ -240,16 +240,15 @@ def test_fp32_normalization_and_scale():
 
 # ------------------------------------------------------- lazy projection --
 
+# Matrices as small as these are projected in one pass over every layer; calls that walk in several passes, their size
+# classes and read-backs, are in test_gpu_lazy_walks.py.
 LAZY_CASES = [("bf16_s32", dict(B=1, L=64, K=4, d=264, V=5003, n_masked=8, masked_frac=None), 11),
               ("bf16_big128", dict(B=2, L=40, K=4, d=520, V=7001, n_masked=16, masked_frac=None), 16),
               ("bf16_big", dict(B=1, L=120, K=4, d=200, V=6007, n_masked=100, masked_frac=None), 17),
-              # 200 positions: the final-layer pass lists 200 rows, which the 256 x 256 tile takes
               ("bf16_big_row_list", dict(B=1, L=240, K=4, d=136, V=3001, n_masked=200, masked_frac=None), 20),
-              # most positions in the band: the passes after the first list 65-256 rows, launched once per
-              # size class (<= 64, <= 128, above) with the count taken on the device
+              # most positions in the band
               ("bf16_size_classes", dict(B=1, L=256, K=5, d=136, V=3001, n_masked=250, masked_frac=None,
                                          sharp=("calibrated", 0.5, 2.5), unstable_frac=0.1), 21),
-              # above 256 positions the second pass reads its count back, later ones run per size class
               ("bf16_readback", dict(B=2, L=160, K=5, d=136, V=3001, n_masked=150, masked_frac=None,
                                      sharp=("calibrated", 0.5, 2.5), unstable_frac=0.1), 22)]
 
@@ -289,7 +288,7 @@ def test_lazy_projection_walking_every_position(name, ov, seed):
 
 
 def test_lazy_pass_over_several_layers():
-    # a pass after the first that takes all the layers left of about 60 positions
+    # about 60 of 250 positions in the band, 8 layers: one pass over all of them
     w = make_workload(CONFIGS["llada_late"].with_(name="lazypass", B=1, L=256, K=8, d=1024, V=20011, n_masked=250,
                                                   masked_frac=None, sharp=("calibrated", -1.0, 1.0), unstable_frac=0.25,
                                                   layer_jitter=0.3), 71)
@@ -297,8 +296,8 @@ def test_lazy_pass_over_several_layers():
 
 
 # Calls that walk in several passes need matrices on which a pass is worth fewer rows than the call has, so these are
-# drawn on the GPU and compared with the eager projection: passes of 1, 2, 4 .. layers with the counts on the device
-# (up to 256 positions) or read back, in every size class.
+# drawn on the GPU and compared with the eager projection: passes with the counts on the device (up to 256 positions)
+# or read back, in every size class. (40 positions of 8 layers are one pass.)
 @pytest.mark.parametrize("B,n,K,dtype,every,norm", [
     (1, 250, 8, "bf16", False, False), (1, 250, 8, "bf16", True, False), (1, 256, 4, "bf16", True, True),
     (2, 190, 6, "bf16", False, True), (2, 190, 6, "bf16", True, False), (1, 40, 8, "bf16", True, False),
@@ -364,8 +363,7 @@ def test_lazy_projection_with_normalization_and_fp32():
     wb = make_workload(CONFIGS["llada_late"].with_(name="lazy_norm", B=1, L=64, K=4, d=264, V=5003, n_masked=8,
                                                    masked_frac=None, sharp=("calibrated",), unstable_frac=0.4), 12)
     _check(wb, dataclasses.replace(O.LLADA, lazy=True), norm=(_gain(wb, 4), 1e-5, True))
-    # 200 positions, most in the band: the passes after the first run once per size class, each
-    # normalizing only its rows
+    # 200 positions, most in the band
     wc = make_workload(CONFIGS["llada_late"].with_(name="lazy_norm_classes", B=1, L=208, K=4, d=200, V=6007,
                                                    n_masked=200, masked_frac=None, sharp=("calibrated", 0.5, 2.5),
                                                    unstable_frac=0.1), 13)
@@ -913,9 +911,9 @@ BAND_HEAVY = dict(sharp=("calibrated", 1.0, 2.2), unstable_frac=0.05)
                                              ("llada_100", 5, BAND_HEAVY)],
                          ids=["llada_25", "llada_100", "llada_batched", "llada_100_band_heavy"])
 def test_lazy_full_size_matches_eager(cfgname, seed, ov, llada_wu):
-    # At the benchmark's sizes (64 masked positions: one streaming pass per layer; 256: passes launched per
-    # size class, with about half the positions in the band for the last case, so that later passes list
-    # more than 128 rows; 3072: counts read back), lazy projection takes the eager path's decisions: tokens,
+    # At the benchmark's sizes (64 and 256 masked positions: passes launched per size class, with about half the
+    # positions in the band for the last case, so that later passes list more than 128 rows; 3072: counts read
+    # back), lazy projection takes the eager path's decisions: tokens,
     # candidacy and, inside the band, persistence and drop. A difference is allowed only at a near-tie of the
     # oracle's statistics for that position (the two paths project a layer with different tile plans).
     w = make_workload(CONFIGS[cfgname].with_(**ov), seed, w_u=llada_wu)

@@ -10,6 +10,7 @@ import pytest
 
 from paper_2609_36452_amd import binding as rpd
 from paper_2609_36452_amd.build import CSRC, INCLUDE
+from tests.lazy_walks import WALKS
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 OUT_OF_MEMORY, INVALID_VALUE = 2, 1
@@ -162,3 +163,19 @@ def test_lazy_counts_above_the_bound_are_waited_for(host):
     assert "sync" not in log[11:] and log[-2:] == ["score300", "commit0"]
     passes = _projections(log)[3:]
     assert passes and all(len(p) > 1 for p in passes)
+
+
+@pytest.mark.parametrize("name,K,B,n,d,V,dtype,every,norm,ties", WALKS, ids=[c[0] for c in WALKS])
+def test_the_shapes_of_the_walking_tests_walk(host, name, K, B, n, d, V, dtype, every, norm, ties):
+    # of the positions n_t are left walking after pass t: counts are waited for above 256 positions, else each pass
+    # after the first is enqueued once per size class
+    counts = [B * n, B * n * 9 // 10, B * n // 4]
+    for bound in (B * n, -1):
+        host.host_reset()
+        for c in counts:
+            host.host_add_count(c)
+        s, log = _call(host, bound, K=K, B=B, n=n + 9, d=d, V=V, dtype=int(dtype == "f32"), flags=3 if every else 1)
+        assert s == 0 and "score%d" % (B * n) in log and log.count("next") >= 1
+        assert log.count("sync") == (bound < 0) + (2 if B * n > 256 else 0)
+        passes = _projections(log)
+        assert len(passes) >= 2 and (B * n > 256 or max(len(p) for p in passes[1:]) >= 2)

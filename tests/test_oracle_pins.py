@@ -18,6 +18,7 @@ import scipy.stats
 
 import oracle as O
 from paper_2609_36452_amd.workload import make_workload, CONFIGS
+from tests.lazy_walks import lazy_from_eager, stop_early
 
 GOLD = os.path.join(os.path.dirname(__file__), "golden")
 
@@ -700,3 +701,23 @@ def test_apply_commit_fills_only_masked_positions():
     # a second iteration flagging the same positions again changes nothing there
     O.apply_commit(mask, canvas, np.array([[1, 1, 0, 1, 0]], np.uint8), np.array([[20, 21, 22, 23, 24]]))
     assert mask.tolist() == [[0, 0, 0, 0, 0]] and canvas.tolist() == [[10, 21, 7, 13, 9]]
+
+
+@pytest.mark.parametrize("every", [False, True])
+@pytest.mark.parametrize("K", [1, 2, 6])
+def test_lazy_results_from_the_eager_statistics(K, every):
+    # the reference that the tests of large lazy calls use is the lazy projection's own result
+    w = make_workload(CONFIGS["tiny"].with_(K=K, sharp=("calibrated",), unstable_frac=0.3), 77 + K)
+    stop_early(w, K)
+    P = O.Params(theta_s=2.5, w=5.0, theta_c=0.3, lazy=True, lazy_all=every)
+    a = O.score_commit_lazy(w.hidden, w.w_u, w.mask, w.cfg.dtype, P)
+    pos, layer = O.layer_stats_masked(w.hidden, w.w_u, w.mask, w.cfg.dtype)
+    b = lazy_from_eager(w.mask, pos, layer, P)
+    assert K < 3 or len(set(a["layers_projected"])) >= 4
+    m = w.mask != 0
+    for k in a:
+        if k == "layer_p_final":     # where a layer disagrees, the eager projection knows the final token's probability
+            continue
+        np.testing.assert_allclose(np.asarray(a[k], float), np.asarray(b[k], float), rtol=1e-12, atol=1e-12,
+                                   equal_nan=True, err_msg=k)
+    assert (a["layer_argmax"][:, m] >= 0).sum() == a["layers_projected"].sum()
