@@ -133,6 +133,46 @@ def test_compaction_inside_the_projection(name, K, bound):
             assert rep.ok(), rep.summary()
 
 
+def _same_on_a_padded_canvas(w, bound, norm=None):
+    """The call on the canvas as it is (compaction inside) and padded with
+    900 unmasked positions a sequence (compaction before): the same bits."""
+    cfg, L = w.cfg, w.cfg.L
+    assert cfg.B * L <= 512 < cfg.B * (L + 900)
+    nothing = np.full((cfg.K, cfg.B, 900, cfg.d), np.nan if cfg.dtype == "f32" else 0x7FC0, w.hidden.dtype)
+    wide = dataclasses.replace(w, cfg=cfg.with_(L=L + 900), hidden=np.concatenate([w.hidden, nothing], 2),
+                               mask=np.concatenate([w.mask, np.zeros((cfg.B, 900), np.uint8)], 1))
+    a = run_gpu(w, O.LLADA, max_masked=bound, norm=norm)
+    b = run_gpu(wide, O.LLADA, max_masked=bound, norm=norm)
+    assert int(a["status"][0]) == int(b["status"][0]) == (1 if w.n_masked > bound else 0)
+    seen = np.cumsum(w.mask.reshape(-1)).reshape(w.mask.shape)
+    m = (w.mask != 0) & (seen <= bound)      # the first `bound` masked positions are scored
+    for k in ("token", "entropy", "confidence", "persistence", "drop", "stability"):
+        np.testing.assert_array_equal(a[k][m], b[k][:, :L][m], err_msg=k)
+    if w.n_masked <= bound:
+        o = run_oracle(w, O.LLADA, norm=norm)
+        rep = compare(a, o, w.mask, O.LLADA, cfg.d)
+        assert rep.ok(), rep.summary()
+
+
+# tiles that begin within a position's layers (128 rows a tile, 3 or 5 layers), as many on each XCD or not; counts that
+# leave tiles without rows
+@pytest.mark.parametrize("K,bound", [(3, 341), (3, 350), (5, 409)])
+def test_compaction_inside_several_fp32_row_tiles(K, bound):
+    for n in (bound, bound - 3, bound // 3, 1, 0, bound + 2):
+        w = make_workload(CONFIGS["llada_late"].with_(name="fc_rows", B=1, L=500, K=K, d=72, V=33003, n_masked=n,
+                                                      dtype="f32", sharp=("calibrated",), unstable_frac=0.3), 95 + n)
+        _same_on_a_padded_canvas(w, bound)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 264), ("bf16", 2056), ("f32", 77), ("f32", 1028)])
+def test_compaction_inside_the_normalization(dtype, d):
+    bound = 22
+    for n in (11, 9, 0, 12):
+        w = make_workload(CONFIGS["llada_late"].with_(name="fc_norm", B=2, L=250, K=3, d=d, V=1500, n_masked=n,
+                                                      dtype=dtype, sharp=("calibrated",), unstable_frac=0.3), 97 + n)
+        _same_on_a_padded_canvas(w, bound, norm=(_gain(w, d), 1e-5, False))
+
+
 # ------------------------------------------------------- fp32 MFMA tiles --
 
 F32_CASES = [
