@@ -443,9 +443,11 @@ static rpd_status score_commit_impl(const rpd_problem* p, const rpd_params* q, c
   }
   a.rowoff = nullptr;
   fill_common(a, q, o);
-  // a lazy call is projected in passes, or all at once where that cannot cost more
+  // a lazy call is projected in passes, or in one over all layers (lazy_one_pass); without a bound that is
+  // decided when the count is known, and the first pass is listed for either
   const bool lazy_call = (q->flags & RPD_PARAM_LAZY) != 0;
-  bool lazy = lazy_call && !rpd::lazy_one_pass(p->dtype, a.K, a.max_masked, a.d, a.V, a.lazy_all);
+  bool lazy = lazy_call &&
+              (p->max_masked < 0 ? a.K > 1 : !rpd::lazy_one_pass(p->dtype, a.K, a.max_masked, a.d, a.V, a.lazy_all));
 
   auto mark = [&](int k) -> hipError_t {
     if (k < n_events && events[k]) return hipEventRecord(static_cast<hipEvent_t>(events[k]), s);

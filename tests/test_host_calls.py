@@ -165,6 +165,16 @@ def test_lazy_counts_above_the_bound_are_waited_for(host):
     assert passes and all(len(p) > 1 for p in passes)
 
 
+def test_a_lazy_call_without_a_bound_decides_by_its_count(host):
+    # 250 of 259 positions: one pass over the whole canvas would not cost more than walking it (six 256-row tiles for
+    # two), one over the 250 would; a bound of 250 walks, and so does no bound
+    shape = dict(K=5, n=259, d=2048, V=40009, flags=LAZY_ALL)
+    for bound, want in ((259, "reduce259"), (250, "score250"), (-1, "score250")):
+        host.host_reset()
+        host.host_add_count(250)
+        assert want in _call(host, bound, **shape)[1], bound
+
+
 @pytest.mark.parametrize("name,K,B,n,d,V,dtype,every,norm,ties", WALKS, ids=[c[0] for c in WALKS])
 def test_the_shapes_of_the_walking_tests_walk(host, name, K, B, n, d, V, dtype, every, norm, ties):
     # of the positions n_t are left walking after pass t: counts are waited for above 256 positions, else each pass
