@@ -105,11 +105,16 @@ typedef enum rpd_status {
  *               paper); 1: normalize it like the others
  *   max_masked  an upper bound on the number of masked positions summed over
  *               the batch, or -1. With -1 the call waits once for the exact
- *               count (and so for the work on the stream before it). If the
- *               bound is exceeded, only the first max_masked masked positions
- *               (batch-major, canvas order) are scored, the results for the
- *               rest are undefined, and RPD_DEVICE_STATUS_MASKED_OVERFLOW is
- *               raised in the optional status word.
+ *               count (and so for the work on the stream before it): it polls
+ *               pinned memory that the kernel with the count writes, for up to
+ *               2 ms, keeping its CPU busy, then synchronises the stream (and
+ *               at once if it cannot use that memory). RPD_OK does not imply
+ *               that the stream was synchronised or that earlier work on it
+ *               succeeded. If the bound is exceeded, only the first
+ *               max_masked masked positions (batch-major, canvas order) are
+ *               scored, the results for the rest are undefined, and
+ *               RPD_DEVICE_STATUS_MASKED_OVERFLOW is raised in the optional
+ *               status word.
  */
 typedef struct rpd_problem {
   int32_t K, B, L, d, V;
@@ -156,19 +161,23 @@ typedef struct rpd_problem {
  * persistence, drop and stability are then not evaluated (persistence -1,
  * drop and stability NaN). Either way tokens, candidacy and commitment are
  * those of the eager projection, and the per-layer outputs of layers never
- * projected hold -1 / NaN. One projection pass takes as many of a position's
- * next layers as cost no more than another pass would (each pass streams W_U
- * again, and up to a few hundred rows that is what it costs), and a call so
- * small that one pass over every layer costs no more than the final layer and
- * the walk makes just that one; the layers below a position's first
+ * projected hold -1 / NaN. One projection pass takes several of a position's
+ * next layers while its rows are few (each pass streams W_U again, and up to a
+ * few hundred rows that is what it costs), and at least 1, 2, 4, .. of them; a
+ * small call projects every layer in one pass, where that costs little more
+ * than the least that walking can. The layers below a position's first
  * disagreement are then read and projected too, and reported as never
- * projected. It pays where the projection is compute-bound (many masked
- * positions). While max_masked is at most 256, every pass reads its count on
- * the device and is launched once per size class the row count may fall in
- * (<= 64, <= 128, <= 256, up to the bound; in fp32 32, 64, 128), all but one
- * exiting at once; above, the previous pass's count is read back (one stream
- * synchronisation) and the pass planned for it. So with max_masked <= 256 the
- * call never synchronises.
+ * projected. Whether positions stop at once or agree on down to the last layer
+ * is not known beforehand: a call whose positions all stop at once can take
+ * longer than it would with one layer a pass, one whose positions agree takes
+ * less (d = 4096, V = 126464, K = 4, 125 positions that all walk: 430 us, with one
+ * layer a pass 372 to 710). Lazy projection pays where the projection is
+ * compute-bound (many masked positions). While max_masked is at most 256, every
+ * pass reads its count on the device and is launched once per size class the
+ * row count may fall in (<= 64, <= 128, <= 192, <= 256, up to the bound; in fp32
+ * 32, 64, 96, 128), all but one exiting at once. Above, the host waits for the
+ * count of the previous pass, as for max_masked = -1, and plans the pass for
+ * it. So with max_masked <= 256 the call never waits.
  *
  * logit_scale multiplies every logit before the softmax statistics (an
  * inverse temperature). The paper reads probabilities before any

@@ -65,7 +65,9 @@ __global__ __launch_bounds__(64 * kLazyReduceWaves) void k_lazy_reduce(
   int cls = 0;
 #pragma unroll
   for (int c = 0; c < kLazyClasses - 1; ++c) cls += m * G > pl.cls.cap[c] ? 1 : 0;
-  const int nvt = cls == 0 ? pl.nvt[0] : (cls == 1 ? pl.nvt[1] : (cls == 2 ? pl.nvt[2] : pl.nvt[3]));
+  int nvt = pl.nvt[0];
+#pragma unroll
+  for (int c = 1; c < kLazyClasses; ++c) nvt = cls == c ? pl.nvt[c] : nvt;
   const int y_fin = st.y[p], k_prev = st.k[p];
   const float pmax_prev = st.pmax[p];
   const int pos = layer_argmax ? rows[p] : 0;

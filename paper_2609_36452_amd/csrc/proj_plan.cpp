@@ -67,77 +67,114 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
   // ranges of the vocabulary (nine row tiles at d = 4096, V = 126464: 864 rows
   // 13.2 -> 7.0 ms, 1136 rows 17.2 -> 9.2; 32 of them at d = 1024, V = 32000:
   // 2.15 ms against 2.16)
-  p.split_rows = p.nrt >= 8 && (dtype != 1 || p.nrt % 8 == 0) ? 1 : 0;
-  p.per_xcd = p.split_rows ? ((p.nrt + 7) / 8) * p.nvt : ((p.nvt + 7) / 8) * p.nrt;
-  p.grid = 8 * p.per_xcd;
+  split_over_xcds(p, p.nrt >= 8 && (dtype != 1 || p.nrt % 8 == 0));
   return p;
+}
+
+void split_over_xcds(ProjPlan& p, bool rows) {
+  p.split_rows = rows ? 1 : 0;
+  p.per_xcd = rows ? ((p.nrt + 7) / 8) * p.nvt : ((p.nvt + 7) / 8) * p.nrt;
+  p.grid = 8 * p.per_xcd;
 }
 
 // ---------------------------------------------------------- lazy passes --
 //
-// How many layers a lazy pass takes, and whether a call walks at all, is decided
-// before anything is known about the walk: positions may stop at the first layer
-// below the final one or agree on down to the last. The two rules below bound
+// How many layers the first pass below the final layer takes, and whether a call
+// walks at all, is decided before anything is known about the walk: positions
+// may stop at once or agree on down to the last layer. The two rules below bound
 // what a call loses against one pass per layer where all stop at once.
 
-// Streaming W_U (6.9 TB/s in bf16, 5.6 in fp32), and one row's matrix time (at 256
-// rows 1.05 PFLOP/s in bf16, 128 TFLOP/s in fp32).
-static double stream_us(int dtype, int d, int V) { return (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / 6.9e6); }
-static double row_us(int dtype, int d, int V) { return 2.0 * V * d / (dtype == 1 ? 128e6 : 1050e6); }
+// A pass over `rows` rows: the rounds of tiles that the busiest XCD's 32 CUs
+// take, each a k-loop over d and a first load and epilogue, or streaming W_U
+// (6.9 TB/s in bf16, 4.6 where its rows are not whole 128-byte lines, by the MFMA
+// tiles 12% less; 5.6 in fp32) if that is more.
+// Fitted to the projection alone at 12 shapes from d = 264 to 4096 and V = 5003 to
+// 152064, 8 to 4096 rows: 396 of 447 times within 25% (at d = 4096, V = 126464 64,
+// 128, 256, 512 and 1024 rows 160, 169, 226, 417 and 800 us, the fit 159, 176, 222,
+// 399 and 792; at d = 656, V = 21723 20, 27, 36, 38 and 63, the fit 19, 41, 46, 36
+// and 66).
+static double pass_us(int dtype, long long rows, int d, int V) {
+  const ProjPlan p = plan_projection(dtype, rows, V);
+  const double st = (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / (d % 64 ? 4.6e6 : 6.9e6));
+  const long long tiles = p.split_rows ? (long long)((p.nrt + 7) / 8) * p.nvt : (long long)((p.nvt + 7) / 8) * p.nrt;
+  const double whole = (double)((tiles + 31) / 32);
+  const double rounds = tiles > 128 ? std::min(whole, tiles / 32.0 + 0.4) : whole;   // in later rounds tiles start apart
+  if (dtype == 1) {
+    const double loop = d / 32.0 * (p.vocab_cap == kF32TileVocabSmall ? 0.42 : 0.5 / 32 * p.rows_per_tile);
+    return 6.0 + std::max(st, rounds * (loop + 5.5));
+  }
+  const double chunks = d / 64.0;
+  if (rows <= kStreamMaxRows) return 9.0 + std::max(st, chunks * (rows <= 32 ? 0.78 : 0.95));
+  const double from_hbm = p.nrt > 1 ? 1.0 : (d % 64 ? 1.8 : 1.12);   // one row tile: no chunk of W_U is found in L2
+  const double chunk = p.rows_per_tile == kBigTileRows ? 1.27 : (p.rows_per_tile == kBigTileRowsSmall ? 1.08 : 0.95);
+  return 6.0 + std::max(1.12 * st, rounds * (chunks * chunk * from_hbm + 17.0));
+}
 
 // What a pass costs beside the projection that runs (its listing, reduction and
 // up to three projections that exit at once), and what a pass does that finds no
 // position (100 and 256 positions at d = 4096, V = 126464 that all stop at the
 // first layer: 377 and 517 us with K = 2, 400 and 530 with K = 4, 436 and 551 with
-// K = 8; the projections of the first two passes take 2 * 171 and 2 * 240).
-static constexpr double kPassUs = 17.0, kEmptyPassUs = 11.0;
+// K = 8; the projections of the first two passes take 2 * 171 and 2 * 240); what a
+// call costs besides its passes.
+static constexpr double kPassUs = 25.0, kEmptyPassUs = 11.0, kCallUs = 20.0;
 
-// Rows up to which layers taken along in vain cost at most half of a pass over
-// few rows, which is what each saves where its positions walk on. At d = 4096,
-// V = 126464 (246 rows), K = 4, half of the positions in the band, one layer a
-// pass -> so: all stopping at once 125 positions 375 -> 445 us, 200 455 -> 510;
-// all agreeing 125 positions 695 -> 460, 200 800 -> 680. Passes of up to twice as
-// many rows lose as much as they gain (200 and 256 positions 600 and 630 us
-// whether they stop or walk; one layer a pass 455 and 455 to 800 and 800).
+// Rows up to which a pass takes further layers of its positions: it then costs
+// at most three quarters more than a pass over few rows, and each layer taken
+// along saves a pass where the positions walk on. (d = 4096, V = 126464: 256 rows.
+// Twice a pass over few rows there, 200 and 256 positions, half of them in the
+// band, that stop at once, K = 4: 600 and 630 us; so 505 and 525; one layer a pass
+// 452 and 452. Agreeing on down to the last layer: 600 and 630; 680 and 705; 800.)
 int lazy_pass_rows(int dtype, int d, int V) {
-  const double r = (1.5 * stream_us(dtype, d, V) + kPassUs) / row_us(dtype, d, V);
-  const int n = (int)std::min(std::max(r, 1.0), dtype == 1 ? 128.0 : (double)kBigTileRows);   // one row tile
-  // whole fp32 tiles: there the matrix time of the rows that pad the last one counts
-  return dtype == 1 && n > 32 ? n / 32 * 32 : n;
+  const int step = dtype == 1 ? 32 : 64, most = 7 * (dtype == 1 ? 128 : kBigTileRows);
+  const double limit = 1.75 * pass_us(dtype, step, d, V) + kPassUs;
+  int n = step;
+  for (int r = step; r <= most; r += step)
+    if (pass_us(dtype, r, d, V) <= limit) n = r;
+  return n;
 }
 
-// A pass over `rows` rows, in tiles of which the busiest XCD has its share. In
-// bf16 a fit: the MFMA tiles read W_U 12% slower than the streaming kernel, and
-// padding rows cost two thirds of a row (d = 4096, V = 126464, the projection alone:
-// 64 rows 153 us, 128 171, 192 193, 256 240, 384 352, 400 418, 512 436, 576 506, 768
-// 634, 1024 822; the fit 156, 174, 191, 240, 339, 410, 437, 486, 634, 831. d = 2048,
-// V = 32000: 64 rows 26, 256 39, 512 53, 1024 111; the fit 25, 36, 60, 110).
-static double pass_us(int dtype, long long rows, int d, int V) {
-  const ProjPlan p = plan_projection(dtype, rows, V);
-  const double st = stream_us(dtype, d, V);
-  const double padded = (double)(p.split_rows ? (p.nrt + 7) / 8 * 8 : p.nrt) * p.rows_per_tile;
-  if (dtype == 1) return 6.0 + std::max(st, padded * row_us(dtype, d, V));
-  const double matrix = 0.25 * st + (0.68 * padded + 0.32 * (double)rows) * 2.0 * V * d / 1345e6;
-  return 6.0 + std::max(rows <= kStreamMaxRows ? st : 1.12 * st, matrix);
+// In the band of positions that walk: whether one pass over every layer of every
+// position, by its bytes and operations alone, costs no more than the final layer
+// and 30 us for each further pass. That leaves out the rounds of tiles and so takes
+// one pass of few rows rather often, as it should: a position in the band is
+// likely, and then the next pass streams W_U again (17 positions, K = 8, d = 1928,
+// V = 136547: 244 us in one pass, 331 walking; 8 in fp32, K = 5, d = 1015, V = 101190:
+// 228 and 281; 64 at d = 4096, V = 126464, K = 4, which walk: 245 against 345, and
+// 196 with none in the band).
+static bool band_in_one_pass(int dtype, int K, long long n, int d, int V) {
+  const double st = (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / 6.7e6), row = 2.0 * V * d;
+  auto us = [&](double rows) {
+    return std::max(st, dtype == 1 ? rows * row / 128e6 : 0.38 * st + rows * row / 1440e6);
+  };
+  const long long worth = std::max(1LL, (long long)((st + 30.0) / (row / (dtype == 1 ? 128e6 : 1050e6))));
+  double least = us((double)n);
+  for (long long rem = K - 1, g = 1; rem > 0; g *= 2, least += 30.0)
+    rem -= n * rem <= 2 * worth ? rem : std::min(std::max(worth / n, g), rem);
+  return us((double)K * n) <= least;
 }
 
 // Whether one pass over every layer of every position takes the place of
-// walking. Where every position walks (walk_all): if it costs at most a fifth
-// more than the least that walking with one layer a pass can, the final layer, one more
-// pass and passes that find no position. (d = 4096, V = 126464, K = 4: 100
-// positions 425 us against 395 where they stop at once and 740 where all agree, 125
-// positions 445 against 385 and 725. At 150 and 200 one pass takes 615 and 790,
-// walking 431 and 510 to 830 and 1000.) In the band: if it costs no more than the
-// final layer, 30 us for the next pass, which takes more as soon as a single
-// position is in the band, and passes that find none.
+// walking. Where every position walks (walk_all), walking costs least if all
+// stop at the first layer, and most if all agree down to the last: one pass is
+// taken up to the middle of the two, but costs no more than 1.3 times the least.
+// (d = 4096, V = 126464, K = 4: 100 positions 415 us in one pass, with one layer a
+// pass 394 to 758; 125 440, 385 to 725; 150 607 and 200 781, where walking, 420 and
+// 480 to 760 and 906, is taken.)
 bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all) {
   if (K == 1) return true;
-  const int n = (int)std::max(cap, 1LL), pr = lazy_pass_rows(dtype, d, V);
+  const int n = (int)std::max(cap, 1LL);
+  if (!walk_all) return band_in_one_pass(dtype, K, n, d, V);
+  const int pr = lazy_pass_rows(dtype, d, V);
   const double one = pass_us(dtype, (long long)K * n, d, V), final_layer = pass_us(dtype, n, d, V);
-  if (walk_all) return one <= 1.2 * (2 * final_layer + kPassUs + (K - 2) * kEmptyPassUs);
-  int passes = 0;
-  for (int rem = K - 1; rem > 0;) rem -= lazy_group(n, rem, lazy_min_group(++passes), pr);
-  return one <= final_layer + 30.0 + (passes - 1) * kEmptyPassUs;
+  double least = final_layer + kCallUs, most = least;
+  for (int t = 1, rem = K - 1; rem > 0; ++t) {
+    const int g = lazy_group(n, rem, lazy_min_group(t), pr);
+    const double walk = kPassUs + pass_us(dtype, (long long)g * n, d, V);
+    least += t > 1 ? kEmptyPassUs : walk;
+    most += walk;
+    rem -= g;
+  }
+  return one + kCallUs <= std::min(0.5 * (least + most), 1.3 * least);
 }
 
 hipError_t launch_projection(const Launch& a, hipStream_t s) {

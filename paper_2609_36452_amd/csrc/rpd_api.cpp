@@ -25,7 +25,7 @@ rpd_status fail(rpd_status s, const char* fmt, ...) {
   return s;
 }
 
-constexpr size_t kHeaderBytes = 256;   // n_masked (0), device status (4), the lazy pass's counts (12..43)
+constexpr size_t kHeaderBytes = 256;   // n_masked (0), device status (4), the lazy pass's counts (12..47)
 constexpr long long kMaxBL = 1LL << 24;
 constexpr int kMaxK = 64;
 // hidden sizes up to 2^20: the MFMA tile's 32-bit byte offsets within its
@@ -268,7 +268,7 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, M
       long long rows_cap = m_host;
       if (t > 0) {
         known = m_host > rpd::kLazyGateRows;
-        const int min_group = known ? 1 : rpd::lazy_min_group(t);
+        const int min_group = rpd::lazy_min_group(t);
         if ((e = rpd::launch_lazy_next(a, dtype, min_group, pass_rows, known ? slot.arm() : nullptr, s)) != hipSuccess)
           return e;
         if (known) {
@@ -294,7 +294,8 @@ hipError_t run_lazy(rpd::Launch& a, int dtype, CountSlot& slot, hipStream_t s, M
         rpd::ProjPlan plans[rpd::kLazyClasses];
         for (int c = 0; c < rpd::kLazyClasses; ++c) {
           const bool last = c == rpd::kLazyClasses - 1;
-          const rpd::Launch ap = pass_launch(a.lazy.tier + c, last ? rows_cap : std::min<long long>(rows_cap, cls.cap[c]));
+          rpd::Launch ap = pass_launch(a.lazy.tier + c, last ? rows_cap : std::min<long long>(rows_cap, cls.cap[c]));
+          rpd::split_over_xcds(ap.plan, false);   // a count far below the bound would fill the row tiles of few XCDs
           plans[c] = ap.plan;
           if (c > 0 && rows_cap <= cls.cap[c - 1]) continue;   // the count cannot be in this class
           if ((e = rpd::launch_projection(ap, s)) != hipSuccess) return e;

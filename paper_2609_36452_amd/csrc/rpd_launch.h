@@ -40,12 +40,12 @@ constexpr int kLazyGateRows = 256;
 // size classes of a lazy pass whose row count only the device knows: the
 // largest count of each class but the last (which holds the rest), by type;
 // each is the largest count of a projection variant
-constexpr int kLazyClasses = 4;
+constexpr int kLazyClasses = 5;
 struct LazyClasses {
   int cap[kLazyClasses - 1];
 };
 inline LazyClasses lazy_classes(int dtype) {
-  return dtype == 1 ? LazyClasses{{32, 64, 128}} : LazyClasses{{64, 128, 192}};
+  return dtype == 1 ? LazyClasses{{32, 64, 96, 128}} : LazyClasses{{64, 128, 192, 256}};
 }
 // largest canvas (B * L) whose compaction the projection does itself with a single row tile
 constexpr int kFusedCompactMax = 2048;
@@ -65,6 +65,8 @@ struct ProjPlan {
 
 // the shape plan for `rows_cap` rows (K * max masked positions)
 ProjPlan plan_projection(int dtype, long long rows_cap, int V);
+// the XCDs own row tiles (rows) or ranges of the vocabulary
+void split_over_xcds(ProjPlan& p, bool rows);
 
 // Lazy projection (proj_plan.cpp): the rows whose matrix time is that of one
 // more pass (at least 1)
@@ -82,10 +84,10 @@ __host__ __device__ inline int lazy_group(int m, int rem, int min_group, int pas
   return g < rem ? g : rem;
 }
 
-// The fewest layers that pass t (from 1) takes of each position whose count only
-// the device knows: twice as many from the third pass on, so that few passes
-// are enqueued where K is large.
-inline int lazy_min_group(int t) { return t < 3 ? 1 : 1 << (t - 2); }
+// The fewest layers that pass t (from 1) takes of each position: 1, then 2, 4
+// and so on. One layer shows which positions stop at once; those that are left
+// have agreed, and few passes are made, and enqueued, where K is large.
+inline int lazy_min_group(int t) { return t < 7 ? 1 << (t - 1) : 64; }
 
 // per-position state of the lazy layerwise projection (lazy.hip)
 struct LazyState {

@@ -15,20 +15,22 @@ WALKS = [
     ("band", 4, 1, 200, 2048, 30011, "bf16", False, False, False),
     ("band_norm", 4, 1, 200, 2048, 30011, "bf16", False, True, False),
     ("band_8_layers", 8, 1, 250, 2048, 20011, "bf16", False, False, False),
-    ("all_classes", 5, 1, 240, 2048, 40009, "bf16", True, False, False),
+    ("all_classes", 5, 1, 230, 2048, 60013, "bf16", True, False, False),
     # more layers than a reduction has waves, and the most the boundary takes: passes of 2, 4, .. layers at least
     ("band_13_layers", 13, 1, 60, 2048, 30011, "bf16", False, False, False),
     ("band_64_layers", 64, 1, 20, 2048, 30011, "bf16", False, False, False),
+    # 2000 rows at most, far fewer in truth
+    ("all_13_layers", 13, 1, 250, 2048, 20011, "bf16", True, False, False),
     # above 256 positions: counts waited for, then on the device
-    ("readback", 5, 2, 150, 2048, 40009, "bf16", True, False, False),
+    ("readback", 5, 2, 150, 2048, 60013, "bf16", True, False, False),
     ("readback_norm", 4, 3, 200, 2048, 20011, "bf16", True, True, False),
     # tied tops: the reduction of a pass resolves them for the forms whose tiles sum in orders of their own
     ("ties_near", 36, 1, 25, 2048, 30011, "bf16", False, False, "near"),
     ("ties_far", 8, 1, 250, 2048, 20011, "bf16", False, False, "far"),
     ("ties_readback", 4, 2, 300, 2048, 20011, "bf16", True, False, "far"),
-    ("f32_all", 4, 1, 100, 2048, 20011, "f32", True, False, False),
+    ("f32_all", 4, 1, 160, 2048, 30011, "f32", True, False, False),
     ("f32_13_layers", 13, 1, 60, 2048, 10007, "f32", True, False, False),
-    ("f32_readback", 5, 2, 150, 2048, 4003, "f32", True, False, False),
+    ("f32_readback", 5, 2, 150, 2048, 10007, "f32", True, False, False),
     ("f32_band_norm", 4, 1, 200, 2048, 4003, "f32", False, True, False),
 ]
 

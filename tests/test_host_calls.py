@@ -126,10 +126,10 @@ def _projections(log):
 
 
 def test_lazy_calls_that_project_every_layer_at_once(host):
-    # Where every position walks, one pass over all layers may cost a fifth more than the least that walking can (d =
-    # 4096, V = 126464: 128 positions at K = 4 are 512 rows, two 256-row tiles; 72 at K = 8 three 192-row tiles)
+    # Where every position walks, one pass over all layers may cost 1.3 times the least that walking can (d = 4096, V =
+    # 126464: 144 positions at K = 4 and 72 at K = 8 are 576 rows, three 192-row tiles)
     one = lambda n, K, flags: "score%d" % n not in _call(host, n, K=K, n=256, flags=flags)[1]   # noqa: E731
-    assert [n for n in range(1, 257) if one(n, 4, LAZY_ALL)] == list(range(1, 129))
+    assert [n for n in range(1, 257) if one(n, 4, LAZY_ALL)] == list(range(1, 145))
     assert [n for n in range(1, 257) if one(n, 8, LAZY_ALL)] == list(range(1, 73))
     assert all(one(n, 2, LAZY_ALL) for n in range(1, 257)) and all(one(n, 1, LAZY) for n in range(1, 257))
     # in the band, where one more pass over few positions is all that walking is likely to take, far fewer
@@ -139,8 +139,7 @@ def test_lazy_calls_that_project_every_layer_at_once(host):
 @pytest.mark.parametrize("K", [3, 4, 8, 20])
 @pytest.mark.parametrize("flags", [LAZY, LAZY_ALL])
 def test_lazy_passes_take_no_more_rows_than_are_worth_one(host, K, flags):
-    # the first two passes after the final layer: the rows of one tile, or a layer of every position; later ones at
-    # least 2, 4 .. layers, and the layers add up
+    # passes after the final layer: the 256 rows of one tile, or 1, 2, 4 .. layers of every position
     for n in (70, 129, 160, 200, 256):
         s, log = _call(host, n, K=K, n=256, flags=flags)
         if "score%d" % n not in log:
@@ -148,30 +147,30 @@ def test_lazy_passes_take_no_more_rows_than_are_worth_one(host, K, flags):
         passes = _projections(log)
         assert s == 0 and passes[0] == [n]
         for t, rows in enumerate(passes[1:], 1):
-            assert max(rows) <= max(256, n * max(1, 2 ** (t - 2))), (n, t, rows)
-            assert sorted(rows) == rows and len(rows) <= 4
-        assert 2 ** (len(passes) - 4) < K
+            assert max(rows) <= max(256, n * 2 ** (t - 1)), (n, t, rows)
+            assert sorted(rows) == rows and len(rows) <= 5
+        assert 2 ** (len(passes) - 2) < K
 
 
 def test_lazy_counts_above_the_bound_are_waited_for(host):
-    # 300 positions, of which 280, 150 and then none walk on: two counts through the slot, then size classes
+    # 300 positions, of which 280 and 150 walk on: two counts through the slot, then size classes
     for c in (300, 280, 150):   # the first by the compaction
         host.host_add_count(c)
     s, log = _call(host, 300, K=6, n=512, flags=LAZY_ALL)
     assert s == 0 and log[:3] == ["compact", "big300", "walk300"]
-    assert log[3:7] == ["next", "sync", "big280", "walk280"] and log[7:11] == ["next", "sync", "big150", "walk150"]
+    assert log[3:7] == ["next", "sync", "big280", "walk280"] and log[7:11] == ["next", "sync", "big300", "walk150"]
     assert "sync" not in log[11:] and log[-2:] == ["score300", "commit0"]
     passes = _projections(log)[3:]
     assert passes and all(len(p) > 1 for p in passes)
 
 
 def test_a_lazy_call_without_a_bound_decides_by_its_count(host):
-    # 250 of 259 positions: one pass over the whole canvas would not cost more than walking it (six 256-row tiles for
-    # two), one over the 250 would; a bound of 250 walks, and so does no bound
-    shape = dict(K=5, n=259, d=2048, V=40009, flags=LAZY_ALL)
-    for bound, want in ((259, "reduce259"), (250, "score250"), (-1, "score250")):
+    # 180 of 200 positions: the whole canvas is projected in one pass (its final layer takes a 256-row tile), the 180
+    # (192 rows) walk; a bound of 180 walks, and so does no bound
+    shape = dict(K=5, n=200, d=2048, V=60013, flags=LAZY_ALL)
+    for bound, want in ((200, "reduce200"), (180, "score180"), (-1, "score180")):
         host.host_reset()
-        host.host_add_count(250)
+        host.host_add_count(180)
         assert want in _call(host, bound, **shape)[1], bound
 
 
