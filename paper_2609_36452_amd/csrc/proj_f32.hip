@@ -44,16 +44,15 @@ constexpr unsigned vm_lgkm_wait(int n) { return (unsigned)((n & 15) | ((n >> 4) 
 // 256 rows 13.84 -> 2.10 ms (128 TFLOP/s; the matrix cores busy 81% of the
 // active cycles, of which the last, partly filled round of tiles takes 6%);
 // 120 rows at d = 256, V = 4096: 36.8 -> 19.1 us. A rotated chunk order
-// (against HBM channel crowding) changed nothing at either size, three or four
-// stages of 64- and 32-row tiles nothing at 256 rows.
+// (against HBM channel crowding) changed nothing at either size; 256 rows in tiles
+// of 64 and 32 rows, with three or four stages, took 2.20 and 2.52 ms.
 //
 // V16: 16-byte loads (d % 4 == 0 and 16-byte aligned sources); else 4-byte
 // loads, a quarter of the bytes per instruction.
 //
 // FC: the workgroup compacts the mask itself (compact_in_workgroup), on a
-// small canvas: the first chunk of W_U is loaded while it
-// does, and the positions sit in the stage loaded last (from chunk 0's barrier
-// on).
+// small canvas: the first chunk of W_U is loaded while it does, and the
+// positions sit in the stage loaded last (from chunk 0's barrier on).
 template <int WV, int NB, int NS, bool V16, bool FC>
 __global__ __launch_bounds__(WV * 64, 2) void k_proj_f32(
     const float* __restrict__ hidden, const float* __restrict__ w_u, const int32_t* __restrict__ rows,
