@@ -12,10 +12,10 @@
 //               only ones whose candidacy the stability test decides, Eq. 5,
 //               a further saving that leaves every decision unchanged) and
 //               whose layers so far all agreed with the final token.
-// A pass takes several layers of each of its positions where that costs no
-// more than another pass would (lazy_group: up to the ridge a pass costs the
-// one stream of W_U, whatever its rows): a position's layers below its first
-// disagreement are then projected and not used. Each pass is the ordinary
+// A pass takes several layers of each of its positions while its rows are few
+// (up to the ridge a pass costs the one stream of W_U, whatever its rows), and
+// at least 1, 2, 4, .. of them (lazy_group): a position's layers below its
+// first disagreement are then projected and not used. Each pass is the ordinary
 // projection over an explicit list of rows (a table of element offsets into
 // the hidden states, or normalized rows), followed by k_lazy_reduce (merge
 // the tile states, walk each position through the pass's layers, in order)
@@ -27,9 +27,9 @@
 // drop and stability NaN). The commitment follows as usual.
 //
 // Against one pass for each layer, at d = 4096, V = 126464, K = 4: a call over
-// 256 positions, those in the band (about 60) walking, 749 -> 490 us (one pass
+// 256 positions, those in the band (about 60) walking, 757 -> 467 us (one pass
 // of 3 layers instead of three, and two sets of empty launches fewer);
-// iterations over 190-230 positions that all walk, 979 -> 920 us.
+// iterations over 190-230 positions that all walk, 987 -> 909 us.
 #include "reduce_device.h"
 
 namespace rpd {

@@ -143,9 +143,9 @@ void fill_common(rpd::Launch& a, const rpd_params* q, const rpd_outputs* o) {
 // idle for 39 us between the compaction and the projection, 10-17 us longer
 // (calls that read the count back, d = 4096, V = 126464: 32 rows 186.9 ->
 // 173.5 us, 256 rows 265 -> 257; lazy over 800 positions at d = 2000, V =
-// 30000: 623 -> 559). The slots are one page for the whole process, allocated on first use
-// and kept; a call takes one and gives it back, and one that finds none (or
-// may not allocate, or is under capture) copies the count as before.
+// 30000: 623 -> 559). The slots are one page for the whole process, allocated
+// on first use and kept; a call takes one and gives it back, and one that finds
+// none (or may not allocate, or is under capture) copies the count as before.
 constexpr int kSlots = 64;
 std::atomic<uint64_t> g_slots_free{~0ull};
 std::once_flag g_slots_once;

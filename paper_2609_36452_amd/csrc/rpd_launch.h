@@ -68,8 +68,8 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V);
 // the XCDs own row tiles (rows) or ranges of the vocabulary
 void split_over_xcds(ProjPlan& p, bool rows);
 
-// Lazy projection (proj_plan.cpp): the rows whose matrix time is that of one
-// more pass (at least 1)
+// Lazy projection (proj_plan.cpp): the rows up to which a pass takes further
+// layers of its positions
 int lazy_pass_rows(int dtype, int d, int V);
 // whether a lazy call over at most `cap` positions projects all K layers of
 // every position in one pass
