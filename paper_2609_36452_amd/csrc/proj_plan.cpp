@@ -6,35 +6,55 @@
 
 namespace rpd {
 
+// Rounds of tiles that the 32 CUs of the busiest XCD take, the XCDs owning row
+// tiles (by_rows) or ranges of the vocabulary; past a few rounds tiles start
+// apart and the last round is seldom a whole one.
+static double tile_rounds(long long nrt, int nvt, bool by_rows) {
+  const long long tiles = by_rows ? (nrt + 7) / 8 * nvt : (nvt + 7) / 8 * nrt;
+  const double whole = (double)((tiles + 31) / 32);
+  return tiles > 128 ? std::min(whole, tiles / 32.0 + 0.4) : whole;
+}
+
 ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
   ProjPlan p{};
+  bool f32_by_rows = false;
   if (rows_cap < 1) rows_cap = 1;
   if (dtype == 1) {   // fp32
-    // The tile height (32..128 rows) whose padded rows cost least, a row of a
-    // shorter tile costing more (it reads W_U more often: 1024 rows at d = 4096,
-    // V = 126464 in tiles of 128, 96, 64 and 32 rows 8.15, 8.38 per padded row,
-    // 8.17 and 8.79 ms; 4096 rows at d = 1024, V = 32000 2.17, 2.21, 2.21 and
-    // 2.33); the tallest of equals. A launch that would leave most of the 256
-    // CUs idle takes 64 x 32 tiles instead.
+    // The tile height (32..128 rows), and whether the XCDs own row tiles or
+    // ranges of the vocabulary, by the rounds of tiles that the busiest XCD
+    // takes (tile_rounds) and what a row costs, a row of a shorter tile costing
+    // more (it reads W_U more often: 1024 rows at d = 4096, V = 126464 in tiles of
+    // 128, 96, 64 and 32 rows 8.15, 8.38 per padded row, 8.17 and 8.79 ms; 4096
+    // rows at d = 1024, V = 32000 2.17, 2.21, 2.21 and 2.33). Of equals the
+    // tallest, and row tiles (32 of them there: 2.15 ms against 2.16). Dealing
+    // whole row tiles wherever there are eight took as long for nine as for
+    // sixteen (864 rows at d = 4096, V = 126464 13.2 ms, 7.0 so). 64 x 32 tiles, which
+    // take 0.84 of a 128 x 32 tile's time, where the launch would leave CUs idle.
     static constexpr struct {
       int rows;
       double cost;   // of a row, against the tallest tile's
     } kHeights[] = {{128, 1.0}, {96, 1.02}, {64, 1.02}, {32, 1.07}};
     p.variant = PROJ_F32;
     p.vocab_cap = kF32TileVocab;
+    p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
     double best = 0.0;
     for (const auto& h : kHeights) {
-      const double cost = (double)((rows_cap + h.rows - 1) / h.rows * h.rows) * h.cost;
-      if (best == 0.0 || cost < best) {
-        best = cost;
-        p.rows_per_tile = h.rows;
+      const long long nrt = (rows_cap + h.rows - 1) / h.rows;
+      for (int by_rows = nrt >= 8 ? 1 : 0; by_rows >= 0; --by_rows) {
+        const double cost = tile_rounds(nrt, p.nvt, by_rows != 0) * h.rows * h.cost;
+        if (best == 0.0 || cost < 0.995 * best) {
+          best = cost;
+          p.rows_per_tile = h.rows;
+          f32_by_rows = by_rows != 0;
+        }
       }
     }
-    p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
-    if ((long long)p.nvt * ((rows_cap + p.rows_per_tile - 1) / p.rows_per_tile) < 256) {
+    const int nvt_small = (V + kF32TileVocabSmall - 1) / kF32TileVocabSmall;
+    if (tile_rounds((rows_cap + 31) / 32, nvt_small, false) * 32 * 0.84 < best) {
       p.vocab_cap = kF32TileVocabSmall;
       p.rows_per_tile = 32;
-      p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
+      p.nvt = nvt_small;
+      f32_by_rows = false;
     }
   } else if (rows_cap <= kStreamMaxRows) {
     // HBM-bound: one row tile holding every projected row, so W_U is read
@@ -63,11 +83,7 @@ ProjPlan plan_projection(int dtype, long long rows_cap, int V) {
     p.nvt = (V + p.vocab_cap - 1) / p.vocab_cap;
   }
   p.nrt = (int)((rows_cap + p.rows_per_tile - 1) / p.rows_per_tile);
-  // fp32: the XCDs own whole row tiles only where each gets as many, else
-  // ranges of the vocabulary (nine row tiles at d = 4096, V = 126464: 864 rows
-  // 13.2 -> 7.0 ms, 1136 rows 17.2 -> 9.2; 32 of them at d = 1024, V = 32000:
-  // 2.15 ms against 2.16)
-  split_over_xcds(p, p.nrt >= 8 && (dtype != 1 || p.nrt % 8 == 0));
+  split_over_xcds(p, dtype == 1 ? f32_by_rows : p.nrt >= 8);
   return p;
 }
 
@@ -89,16 +105,14 @@ void split_over_xcds(ProjPlan& p, bool rows) {
 // (6.9 TB/s in bf16, 4.6 where its rows are not whole 128-byte lines, by the MFMA
 // tiles 12% less; 5.6 in fp32) if that is more.
 // Fitted to the projection alone at 12 shapes from d = 264 to 4096 and V = 5003 to
-// 152064, 8 to 4096 rows: 396 of 447 times within 25% (at d = 4096, V = 126464 64,
+// 152064, 8 to 4096 rows: 402 of 447 times within 25% (at d = 4096, V = 126464 64,
 // 128, 256, 512 and 1024 rows 160, 169, 226, 417 and 800 us, the fit 159, 176, 222,
 // 399 and 792; at d = 656, V = 21723 20, 27, 36, 38 and 63, the fit 19, 41, 46, 36
 // and 66).
 static double pass_us(int dtype, long long rows, int d, int V) {
   const ProjPlan p = plan_projection(dtype, rows, V);
   const double st = (double)V * d * (dtype == 1 ? 4 / 5.6e6 : 2 / (d % 64 ? 4.6e6 : 6.9e6));
-  const long long tiles = p.split_rows ? (long long)((p.nrt + 7) / 8) * p.nvt : (long long)((p.nvt + 7) / 8) * p.nrt;
-  const double whole = (double)((tiles + 31) / 32);
-  const double rounds = tiles > 128 ? std::min(whole, tiles / 32.0 + 0.4) : whole;   // in later rounds tiles start apart
+  const double rounds = tile_rounds(p.nrt, p.nvt, p.split_rows != 0);
   if (dtype == 1) {
     const double loop = d / 32.0 * (p.vocab_cap == kF32TileVocabSmall ? 0.42 : 0.5 / 32 * p.rows_per_tile);
     return 6.0 + std::max(st, rounds * (loop + 5.5));

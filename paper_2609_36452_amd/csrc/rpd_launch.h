@@ -32,8 +32,8 @@ constexpr int kStreamTileVocab = 256;
 constexpr int kStreamMaxRows = 64;
 // rows of the smaller MFMA tiles
 constexpr int kBigTileRowsSmall = 192, kBigTileRowsMid = 128;
-// vocabulary rows of the fp32 tiles: the ordinary ones and, for launches too
-// small to fill the GPU, the small one
+// vocabulary rows of the fp32 tiles: the ordinary ones and, for launches that
+// would leave CUs idle, the small one
 constexpr int kF32TileVocab = 128, kF32TileVocabSmall = 64;
 // largest bound on a lazy call's positions below which the host reads no count back
 constexpr int kLazyGateRows = 256;

@@ -23,6 +23,7 @@ import torch
 import oracle as O
 from paper_2609_36452_amd import binding as rpd
 from paper_2609_36452_amd.workload import CONFIGS, draw_unembedding, make_workload, round_bf16_bits
+from tests.f32_forms import F32_FORMS
 from tests.gpu_util import gpu_params, note, run_gpu, run_oracle, to_device
 from tests.parity import compare, gap_tol, ENTROPY_TOL, CONF_TOL
 
@@ -133,14 +134,14 @@ def test_compaction_inside_the_projection(name, K, bound):
             assert rep.ok(), rep.summary()
 
 
-def _same_on_a_padded_canvas(w, bound, norm=None):
+def _same_on_a_padded_canvas(w, bound, norm=None, pad=900):
     """The call on the canvas as it is (compaction inside) and padded with
-    900 unmasked positions a sequence (compaction before): the same bits."""
+    unmasked positions (compaction before): the same bits."""
     cfg, L = w.cfg, w.cfg.L
-    assert cfg.B * L <= 512 < cfg.B * (L + 900)
-    nothing = np.full((cfg.K, cfg.B, 900, cfg.d), np.nan if cfg.dtype == "f32" else 0x7FC0, w.hidden.dtype)
-    wide = dataclasses.replace(w, cfg=cfg.with_(L=L + 900), hidden=np.concatenate([w.hidden, nothing], 2),
-                               mask=np.concatenate([w.mask, np.zeros((cfg.B, 900), np.uint8)], 1))
+    assert cfg.B * L <= 512 < cfg.B * (L + pad)
+    nothing = np.full((cfg.K, cfg.B, pad, cfg.d), np.nan if cfg.dtype == "f32" else 0x7FC0, w.hidden.dtype)
+    wide = dataclasses.replace(w, cfg=cfg.with_(L=L + pad), hidden=np.concatenate([w.hidden, nothing], 2),
+                               mask=np.concatenate([w.mask, np.zeros((cfg.B, pad), np.uint8)], 1))
     a = run_gpu(w, O.LLADA, max_masked=bound, norm=norm)
     b = run_gpu(wide, O.LLADA, max_masked=bound, norm=norm)
     assert int(a["status"][0]) == int(b["status"][0]) == (1 if w.n_masked > bound else 0)
@@ -176,7 +177,7 @@ def test_compaction_inside_the_normalization(dtype, d):
 # ------------------------------------------------------- fp32 MFMA tiles --
 
 F32_CASES = [
-    # projected rows 32, 64, 96 and 128 a tile, then the small tile (launches of under 256 tiles); hidden sizes of
+    # one to eight row tiles of 32 rows, then the small tile (taller ones: f32_forms.py); hidden sizes of
     # whole 32-wide chunks, with a tail, of one chunk, of none, and (d % 4 != 0) through 4-byte loads
     ("tile32", dict(B=1, L=40, K=4, d=96, V=33001, n_masked=8), 61),
     ("tile64_odd_d", dict(B=1, L=40, K=3, d=67, V=32900, n_masked=20), 62),
@@ -203,6 +204,15 @@ def test_f32_tiles(name, ov, seed):
     for k in a:
         np.testing.assert_array_equal(a[k][..., w.mask != 0] if a[k].ndim >= 2 else a[k],
                                       b[k][..., w.mask != 0] if b[k].ndim >= 2 else b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("name,rows,vocab,ov,seed", F32_FORMS, ids=[c[0] for c in F32_FORMS])
+def test_f32_forms(name, rows, vocab, ov, seed):
+    test_f32_tiles(name, ov, seed)
+    base = CONFIGS["tiny"].with_(name="f32_" + name, sharp=("calibrated",), unstable_frac=0.3, **ov)
+    n = base.n_masked
+    for k in (n, n - 3, 0, n + 2):      # of the bound, fewer, none, more
+        _same_on_a_padded_canvas(make_workload(base.with_(n_masked=k), seed + 1), base.B * n, pad=2100)
 
 
 # ------------------------------------------------------------ RPD-block --

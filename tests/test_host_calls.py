@@ -10,6 +10,7 @@ import pytest
 
 from paper_2609_36452_amd import binding as rpd
 from paper_2609_36452_amd.build import CSRC, INCLUDE
+from tests.f32_forms import F32_FORMS
 from tests.lazy_walks import WALKS
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -109,6 +110,21 @@ def test_fp32_tile_height_by_the_cost_of_its_rows(host):
     rows = (32, 48, 96, 128, 160, 208, 224, 240, 256, 288, 320, 352, 384, 544, 640, 736, 800, 864, 992, 1136)
     assert [_plan(host, 1, r, 126464).rows_per_tile for r in rows] == \
         [32, 64, 96, 128, 32, 32, 32, 128, 128, 96, 64, 32, 128, 32, 128, 128, 64, 96, 128, 128]
+
+
+@pytest.mark.parametrize("name,rows,vocab,ov,seed", F32_FORMS, ids=[c[0] for c in F32_FORMS])
+def test_the_shapes_of_the_fp32_forms_take_them(host, name, rows, vocab, ov, seed):
+    p = _plan(host, 1, ov["K"] * ov["B"] * ov["n_masked"], ov["V"])
+    assert (p.rows_per_tile, p.vocab_cap, p.split_rows) == (rows, vocab, int(name.endswith("row_split")))
+    assert p.nrt == {"tile128_two_row_tiles": 2, "tile64_row_split": 16, "small": 4}.get(name, 1)
+
+
+def test_fp32_tiles_by_rounds_on_the_busiest_xcd(host):
+    # V = 15460: 121 vocabulary tiles, 16 on an XCD: two row tiles of 32 or 64 rows are one round of its 32 CUs; at V =
+    # 3285 (26, 4 on an XCD; or 52 of 64 vocabulary rows, 7) four to seven row tiles of 32
+    assert [_plan(host, 1, r, 15460).rows_per_tile for r in (32, 64, 96, 128)] == [32, 32, 64, 64]
+    assert [(p.rows_per_tile, p.vocab_cap) for p in (_plan(host, 1, r, 3285) for r in (32, 128, 200))] == \
+        [(32, 64), (32, 64), (32, 128)]
 
 
 LAZY, LAZY_ALL = 1, 3
