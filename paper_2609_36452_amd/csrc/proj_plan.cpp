@@ -175,7 +175,7 @@ static bool band_in_one_pass(int dtype, int K, long long n, int d, int V) {
 // pass 394 to 758; 125 440, 385 to 725; 150 607 and 200 781, where walking, 420 and
 // 480 to 760 and 906, is taken.)
 bool lazy_one_pass(int dtype, int K, long long cap, int d, int V, bool walk_all) {
-  if (K == 1) return true;
+  if (K == 1 || (walk_all && K == 2)) return true;   // two layers are projected whatever they hold
   const int n = (int)std::max(cap, 1LL);
   if (!walk_all) return band_in_one_pass(dtype, K, n, d, V);
   const int pr = lazy_pass_rows(dtype, d, V);

@@ -148,6 +148,8 @@ def test_lazy_calls_that_project_every_layer_at_once(host):
     assert [n for n in range(1, 257) if one(n, 4, LAZY_ALL)] == list(range(1, 145))
     assert [n for n in range(1, 257) if one(n, 8, LAZY_ALL)] == list(range(1, 73))
     assert all(one(n, 2, LAZY_ALL) for n in range(1, 257)) and all(one(n, 1, LAZY) for n in range(1, 257))
+    # two layers of positions that all walk are projected whatever they hold
+    assert all("reduce%d" % n in _call(host, n, K=2, n=n, d=1536, V=31574, flags=LAZY_ALL)[1] for n in range(2, 900, 40))
     # in the band, where one more pass over few positions is all that walking is likely to take, far fewer
     assert not one(64, 4, LAZY) and one(24, 4, LAZY)
 
